@@ -283,8 +283,8 @@ int axis12_blocks(const Grid& g, int axis, int elem_bytes, int dir);
 // of length N; 3: half length N/2 for an even N, full length for an odd N,
 // which takes the full-spectrum transforms): every N = 2^a 3^b 5^c 7^d in
 // [3, 1024] (instantiated register-resident kernels for the powers of two
-// and the lengths fft_mixed_f64/f32.hip list, the LDS-resident kernels of
-// fft_any.hip for the rest), and on axes 1 and 2 also 1 and 2 (2D and 1D
+// and the lengths fft_mixed_f64/f32.hip list, the in-place LDS kernels of
+// fft_any.h for the rest), and on axes 1 and 2 also 1 and 2 (2D and 1D
 // grids)
 bool fft_extent_supported(int N, int axis);
 

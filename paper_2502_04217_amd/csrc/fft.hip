@@ -15,7 +15,7 @@
 //              with the K epilogue q = K p and the p.q partial sums
 // The pencil FFT kernels (Stockham stages, fft_kernels.h) are instantiated
 // here for power-of-two lengths and in fft_mixed_f64/f32.hip for lengths with odd
-// factors; fft_any.hip serves the other 7-smooth lengths.  Strided passes map consecutive lanes to consecutive pencils, so
+// factors; fft_any.h serves the other 7-smooth lengths.  Strided passes map consecutive lanes to consecutive pencils, so
 // every global access is a run of TM contiguous complex numbers.
 #include "fft_kernels.h"
 
@@ -298,11 +298,11 @@ int axis12_blocks(const Grid& g, int axis, int elem_bytes, int dir) {
 bool fft_extent_supported(int N, int axis) {
   AnyPlan pl;
   if (N > kAnyMaxLen) return false;
-  if (axis != 3) return N >= 1 && (templated12(N) || any_plan(N, pl));
+  if (axis != 3) return N >= 1 && (templated12(N) || any_plan(N, 16, pl));
   // an odd N3 takes full-length complex pencils, an even one half-length
   // pencils of the real transforms
-  if (N % 2 == 1) return N >= 3 && (templated12(N) || any_plan(N, pl));
-  return N >= 4 && (templated3(N / 2) || any_plan(N / 2, pl));
+  if (N % 2 == 1) return N >= 3 && (templated12(N) || any_plan(N, 16, pl));
+  return N >= 4 && (templated3(N / 2) || any_plan(N / 2, 16, pl));
 }
 
 template <typename T>

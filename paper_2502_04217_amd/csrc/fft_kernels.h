@@ -2,7 +2,7 @@
 // instantiates them for power-of-two pencil lengths, fft_mixed_f64.hip and
 // fft_mixed_f32.hip for lengths with odd factors 3, 5 and 7 (the
 // non-power-of-two grids of the paper's synthetic size table, small grids
-// that exercise each radix, and odd extents on axes 1 and 2); fft_any.hip
+// that exercise each radix, and odd extents on axes 1 and 2); fft_any.h
 // serves the other lengths 2^a 3^b 5^c 7^d up to 1024 through the same
 // helpers.
 //
@@ -981,16 +981,25 @@ inline bool templated3(int L) {
   return false;
 }
 
-// Every other length 2^a 3^b 5^c 7^d up to kAnyMaxLen: the passes with the
-// pencils in LDS and a radix plan computed at launch (fft_any.hip).
+// Every other length 2^a 3^b 5^c 7^d up to kAnyMaxLen: in-place passes with a
+// radix plan computed at launch (fft_any.h).
 constexpr int kAnyMaxLen = 1024;
+constexpr int kAnyMaxStages = 5;
 struct AnyPlan {
-  int L;        // pencil length
-  int nst;      // stages
-  int r[12];    // radix of each stage: 8, then 4 or 2, then 3, 5, 7
+  int L;                        // pencil length
+  int nst;                      // stages (at least 2: the first may have radix 1)
+  int nt;                       // threads per pencil
+  int tmlog;                    // log2 of the pencils per workgroup
+  int r[kAnyMaxStages];         // radix R_s of each stage
+  int ms[kAnyMaxStages];        // B_s / R_s, B_s = L / (R_0 .. R_{s-1}): the stride of a butterfly's values
+  int step[kAnyMaxStages];      // L / B_s: the stage's unit in the length-L twiddle table
+  unsigned mm[kAnyMaxStages];   // ceil(2^32 / ms)
+  unsigned rm[kAnyMaxStages];   // ceil(2^32 / r)
+  unsigned hm, lm;              // ceil(2^32 / (L / 2 + 1)), ceil(2^32 / L)
 };
-// false when L has a prime factor above 7 or lies outside [1, kAnyMaxLen]
-bool any_plan(int L, AnyPlan& pl);
+// false when L has a prime factor above 7 or lies outside [1, kAnyMaxLen];
+// w: complex size in bytes
+bool any_plan(int L, int w, AnyPlan& pl);
 // pencils per workgroup at complex size w
 int any_tm(int w, int L);
 template <typename T, int AX, int DIR, class Epi>

@@ -19,10 +19,10 @@
  *    N1 and N2 may also be 1 or 2, so a 2D problem is the grid 1 x N2 x N3
  *    and a 1D one 1 x 1 x N3.  Any axis may be odd (the odd-N case of the
  *    parametrisation, section "Problem formulation": no Nyquist index on
- *    that axis; an odd N3 runs the transforms on the whole spectrum, with
- *    twice the bytes of the half-spectrum passes, and when N1*N2*N3 is odd
- *    the library adds internally one coordinate with no data, a zero column
- *    of A, which the solution sets to 0).  n = N1*N2*N3.
+ *    that axis; an odd N3 runs its rows two by two through complex
+ *    transforms of length N3, and when N1*N2*N3 is odd the library adds
+ *    internally one coordinate with no data, a zero column of A, which the
+ *    solution sets to 0).  n = N1*N2*N3.
  *    Other extents return CSIPM_EUNSUPPORTED.
  *  - Real-space arrays are row-major [N1][N2][N3] (index j3 fastest).
  *  - beta-space arrays ("external beta layout") are row-major [N1][N2][N3]
@@ -452,8 +452,7 @@ csipm_status csipm_pc_correction(csipm_ctx* ctx, double* d_c);
  * a solve launches its PCG iterations; the direct-launch time when the
  * graph cannot be recorded), and in ms_out[6] the same with the applies
  * launched directly.  ms_out holds CSIPM_KAPPLY_PASSES + 2 values.
- * Synchronises.  CSIPM_EUNSUPPORTED for an odd N3 (whose K-apply
- * is the full-spectrum transforms). */
+ * Synchronises.  CSIPM_EUNSUPPORTED for an odd N3. */
 #define CSIPM_KAPPLY_PASSES 5
 csipm_status csipm_profile_kapply(csipm_ctx* ctx, int precision, int reps, double* ms_out);
 

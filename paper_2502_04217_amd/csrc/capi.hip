@@ -172,18 +172,16 @@ csipm_status sync_scalars(csipm_ctx* c, const char* where) {
 }
 
 // partial sums of one K-apply: one per workgroup of the axis-1 forward pass
-// (of the unmap pass for an odd N3)
 size_t k_partials(int n1, int n2, int n3) {
   const Grid g = make_grid(n1, n2, n3);
-  if (g.odd3()) return (size_t)cp_blocks(g) + 64;
   return (size_t)std::max(axis12_blocks(g, 1, 16, -1), axis12_blocks(g, 1, 8, -1)) + 64;
 }
 
 size_t layout(Carver& cv, csipm_ctx* c, int n1, int n2, int n3) {
   const Grid g = make_grid(n1, n2, n3);
   const size_t n = (size_t)g.n;
-  // FFT scratch: the half spectrum (n reals), or the whole spectrum for an odd N3
-  const size_t nw = g.odd3() ? std::max(n, (size_t)(2 * g.nr)) : n;
+  // FFT scratch: the half spectrum (n reals; n1 n2 (n3 + 1) for an odd N3)
+  const size_t nw = std::max(n, (size_t)2 * n1 * n2 * g.m);
   const size_t ntw = (size_t)n1 + n2 + n3 / 2 + n3;
   double** d64[] = {&c->beta, &c->z, &c->nu1, &c->nu2, &c->xi, &c->hb, &c->sig1, &c->sig2, &c->rhb, &c->rhz,
                     &c->dxb, &c->dxz, &c->diagH, &c->rb, &c->rz, &c->zb, &c->zz, &c->pb, &c->pz, &c->qb,
@@ -217,86 +215,55 @@ const Twiddles<double>& tw<double>(csipm_ctx* c) { return c->T64; }
 template <>
 const Twiddles<float>& tw<float>(csipm_ctx* c) { return c->T32; }
 
-// out = H in (internal layout), work = FFT scratch; out may not equal in
-// (the axis-1 inverse pass reads the mirror rows of the m = 0 plane).
+// out = H in (internal layout; ext: external), work = FFT scratch; out may
+// not equal in (the axis-1 inverse pass reads the mirror rows of the m = 0
+// plane).
 template <typename T>
-void op_H(csipm_ctx* c, const T* in, T* out, T* work) {
+void op_H(csipm_ctx* c, const T* in, T* out, T* work, bool ext = false) {
   const Grid& g = c->g;
-  if (g.odd3()) {
-    KT(c, PN(T, "cp_map"), cp_map<T>(g, in, work, nullptr, c->s));
-    KT(c, PN(T, "cp_inv"), cp_passes<T>(g, +1, work, tw<T>(c), nullptr, c->s));
-    KT(c, PN(T, "cp_mask"), cp_mask<T>(g, work, c->mask, nullptr, c->s));
-    KT(c, PN(T, "cp_fwd"), cp_passes<T>(g, -1, work, tw<T>(c), nullptr, c->s));
-    KT(c, PN(T, "cp_unmap"), cp_unmap<T>(g, work, out, EPI_NONE, nullptr, nullptr, c->s));
-    return;
-  }
-  KT(c, PN(T, "axis1_inv"), launch_axis12<T>(g, 1, +1, in, work, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s));
+  KT(c, PN(T, "axis1_inv"), launch_axis12<T>(g, 1, +1, in, work, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s, ext));
   KT(c, PN(T, "axis2_inv"), launch_axis12<T>(g, 2, +1, work, work, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s));
   KT(c, PN(T, "axis3"), launch_axis3<T>(g, A3_FULL, work, work, c->mask, tw<T>(c), nullptr, c->s));
   KT(c, PN(T, "axis2_fwd"), launch_axis12<T>(g, 2, -1, work, work, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s));
-  KT(c, PN(T, "axis1_fwd"), launch_axis12<T>(g, 1, -1, work, out, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s));
+  KT(c, PN(T, "axis1_fwd"), launch_axis12<T>(g, 1, -1, work, out, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s, ext));
 }
 
-// x = A in (real grid, row-major), work = FFT scratch (must differ from x).
+// x = A in (real grid, row-major; in in the external layout), work = FFT
+// scratch (must differ from x).
 template <typename T>
 void op_A(csipm_ctx* c, const T* in, T* x, T* work) {
   const Grid& g = c->g;
-  if (g.odd3()) {
-    cp_map<T>(g, in, work, nullptr, c->s);
-    cp_passes<T>(g, +1, work, tw<T>(c), nullptr, c->s);
-    cp_real<T>(g, work, x, c->s);
-    return;
-  }
-  launch_axis12<T>(g, 1, +1, in, work, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s);
+  launch_axis12<T>(g, 1, +1, in, work, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s, true);
   launch_axis12<T>(g, 2, +1, work, work, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s);
   launch_axis3<T>(g, A3_C2R, work, x, nullptr, tw<T>(c), nullptr, c->s);
 }
 
-// out = A^T x (internal layout).
+// out = A^T x (internal layout; ext: external).
 template <typename T>
-void op_At(csipm_ctx* c, const T* x, T* out, T* work) {
+void op_At(csipm_ctx* c, const T* x, T* out, T* work, bool ext = false) {
   const Grid& g = c->g;
-  if (g.odd3()) {
-    cp_cplx<T>(g, x, work, c->s);
-    cp_passes<T>(g, -1, work, tw<T>(c), nullptr, c->s);
-    (void)cp_unmap<T>(g, work, out, EPI_NONE, nullptr, nullptr, c->s);
-    return;
-  }
   launch_axis3<T>(g, A3_R2C, x, work, nullptr, tw<T>(c), nullptr, c->s);
   launch_axis12<T>(g, 2, -1, work, work, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s);
-  launch_axis12<T>(g, 1, -1, work, out, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s);
+  launch_axis12<T>(g, 1, -1, work, out, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s, ext);
 }
 
-size_t k_partials(int n1, int n2, int n3);
-
-// q = K p with p.q partials in c->partK; returns the number of partials.
+// q = K p with p.q partials in c->partK; returns the number of partials (ext:
+// p and q in the external layout).
 template <typename T>
 int op_K(csipm_ctx* c, const T* pb, const T* pz, const T* s1, const T* s2, T* qb, T* qz, T* work,
-         const int* skip, const PUpd<T>* u = nullptr) {
+         const int* skip, const PUpd<T>* u = nullptr, bool ext = false) {
   const Grid& g = c->g;
   const int ps = (int)k_partials(g.n1, g.n2, g.n3);
   EpiArgs<T> ka{KArgs<T>{pb, pz, s1, s2, qb, qz, u ? *u : PUpd<T>{}}, RArgs{}, c->partK, ps};
-  if (g.odd3()) {
-    if (u)
-      KT(c, PN(T, "cp_pupd"),
-         cp_pupdate<T>(g, u->pb, u->pz, u->zb, u->zz, u->beta, skip, c->s));
-    KT(c, PN(T, "cp_map"), cp_map<T>(g, pb, work, skip, c->s));
-    KT(c, PN(T, "cp_inv"), cp_passes<T>(g, +1, work, tw<T>(c), skip, c->s));
-    KT(c, PN(T, "cp_mask"), cp_mask<T>(g, work, c->mask, skip, c->s));
-    KT(c, PN(T, "cp_fwd"), cp_passes<T>(g, -1, work, tw<T>(c), skip, c->s));
-    int nb = 0;
-    KT(c, PN(T, "cp_unmap_K"), nb = cp_unmap<T>(g, work, nullptr, EPI_K, &ka, skip, c->s));
-    return nb;
-  }
   const int nb5 = axis12_blocks(g, 1, (int)sizeof(cx<T>), -1);
   // (the passes that apply the direction update are timed under their own names)
   KT(c, u ? PN(T, "axis1_inv_P") : PN(T, "axis1_inv"),
-     launch_axis12<T>(g, 1, +1, pb, work, tw<T>(c), EPI_NONE, u ? &ka : nullptr, skip, c->s));
+     launch_axis12<T>(g, 1, +1, pb, work, tw<T>(c), EPI_NONE, u ? &ka : nullptr, skip, c->s, ext));
   KT(c, PN(T, "axis2_inv"), launch_axis12<T>(g, 2, +1, work, work, tw<T>(c), EPI_NONE, nullptr, skip, c->s));
   KT(c, PN(T, "axis3"), launch_axis3<T>(g, A3_FULL, work, work, c->mask, tw<T>(c), skip, c->s));
   KT(c, PN(T, "axis2_fwd"), launch_axis12<T>(g, 2, -1, work, work, tw<T>(c), EPI_NONE, nullptr, skip, c->s));
   KT(c, u ? PN(T, "axis1_fwd_KP") : PN(T, "axis1_fwd_K"),
-     launch_axis12<T>(g, 1, -1, work, work, tw<T>(c), EPI_K, &ka, skip, c->s));
+     launch_axis12<T>(g, 1, -1, work, work, tw<T>(c), EPI_K, &ka, skip, c->s, ext));
   return nb5;
 }
 
@@ -310,17 +277,6 @@ void op_Kr(csipm_ctx* c, const float* pcc) {
   RArgs ra{c->dxb, c->dxz, c->sig1, c->sig2, c->rhb, c->rhz, pcc, c->rb};
   EpiArgs<double> ea{KArgs<double>{}, ra, c->partK, ps};
   double* work = c->work;
-  if (g.odd3()) {
-    int nb = 0;
-    KT(c, "cp_map.f64", cp_map<double>(g, c->dxb, work, nullptr, c->s));
-    KT(c, "cp_inv.f64", cp_passes<double>(g, +1, work, c->T64, nullptr, c->s));
-    KT(c, "cp_mask.f64", cp_mask<double>(g, work, c->mask, nullptr, c->s));
-    KT(c, "cp_fwd.f64", cp_passes<double>(g, -1, work, c->T64, nullptr, c->s));
-    KT(c, "cp_unmap_R.f64", nb = cp_unmap<double>(g, work, nullptr, EPI_R, &ea, nullptr, c->s));
-    KT(c, "fin_sum", fin_sum(c->partK, nb, c->scal + S_REF, c->s));
-    KT(c, "fin_max", fin_max(c->partK + ps, nb, c->scal + S_REFINF, c->s));
-    return;
-  }
   const int nb5 = axis12_blocks(g, 1, 16, -1);
   KT(c, "axis1_inv.f64", launch_axis12<double>(g, 1, +1, c->dxb, work, c->T64, EPI_NONE, nullptr, nullptr, c->s));
   KT(c, "axis2_inv.f64", launch_axis12<double>(g, 2, +1, work, work, c->T64, EPI_NONE, nullptr, nullptr, c->s));
@@ -711,8 +667,7 @@ csipm_status csipm_create(csipm_ctx** out, int n1, int n2, int n3, const double*
   // diag(M_perp^T M_perp) from A^T(mask), through the external layout (the
   // coordinate without data, if any, gets 0)
   obs_to_double(d_observed, c->rb, nr, c->s);
-  op_At<double>(c, c->rb, c->zb, c->work);
-  launch_to_external<double, double>(g, c->zb, c->zz, c->s);
+  op_At<double>(c, c->rb, c->zz, c->work, true);
   diag_h(c->zz, c->rz, n1, n2, n3, (double)c->nobs / (double)nr, c->s);
   launch_to_internal<double, double>(g, c->rz, c->diagH, c->s);
   fill<float>(c->pc_c, 1.0f, n, c->s);
@@ -1397,67 +1352,42 @@ csipm_status csipm_get_log(csipm_ctx* c, csipm_iter_log* host_buf, int max_recor
   return CSIPM_OK;
 }
 
+// The operator applies read and write the caller's arrays in the axis-1
+// passes themselves.
 csipm_status csipm_apply_A(csipm_ctx* c, const void* d_beta, void* d_x, int precision) {
   if (!c || !d_beta || !d_x) return CSIPM_EINVAL;
-  if (precision == CSIPM_FP64) {
-    launch_to_internal<double, double>(c->g, (const double*)d_beta, c->pb, c->s);
-    op_A<double>(c, c->pb, (double*)d_x, c->work);
-  } else if (precision == CSIPM_FP32) {
-    launch_to_internal<float, float>(c->g, (const float*)d_beta, c->fpb, c->s);
-    op_A<float>(c, c->fpb, (float*)d_x, c->fwork);
-  } else {
-    return fail(c, CSIPM_EINVAL, "precision");
-  }
+  if (precision == CSIPM_FP64) op_A<double>(c, (const double*)d_beta, (double*)d_x, c->work);
+  else if (precision == CSIPM_FP32) op_A<float>(c, (const float*)d_beta, (float*)d_x, c->fwork);
+  else return fail(c, CSIPM_EINVAL, "precision");
   return hip_check(c, "apply_A");
 }
 
 csipm_status csipm_apply_At(csipm_ctx* c, const void* d_x, void* d_beta, int precision) {
   if (!c || !d_beta || !d_x) return CSIPM_EINVAL;
-  if (precision == CSIPM_FP64) {
-    op_At<double>(c, (const double*)d_x, c->qb, c->work);
-    launch_to_external<double, double>(c->g, c->qb, (double*)d_beta, c->s);
-  } else if (precision == CSIPM_FP32) {
-    op_At<float>(c, (const float*)d_x, c->fqb, c->fwork);
-    launch_to_external<float, float>(c->g, c->fqb, (float*)d_beta, c->s);
-  } else {
-    return fail(c, CSIPM_EINVAL, "precision");
-  }
+  if (precision == CSIPM_FP64) op_At<double>(c, (const double*)d_x, (double*)d_beta, c->work, true);
+  else if (precision == CSIPM_FP32) op_At<float>(c, (const float*)d_x, (float*)d_beta, c->fwork, true);
+  else return fail(c, CSIPM_EINVAL, "precision");
   return hip_check(c, "apply_At");
 }
 
 csipm_status csipm_apply_H(csipm_ctx* c, const void* d_beta, void* d_y, int precision) {
   if (!c || !d_beta || !d_y) return CSIPM_EINVAL;
-  if (precision == CSIPM_FP64) {
-    launch_to_internal<double, double>(c->g, (const double*)d_beta, c->pb, c->s);
-    op_H<double>(c, c->pb, c->qb, c->work);
-    launch_to_external<double, double>(c->g, c->qb, (double*)d_y, c->s);
-  } else if (precision == CSIPM_FP32) {
-    launch_to_internal<float, float>(c->g, (const float*)d_beta, c->fpb, c->s);
-    op_H<float>(c, c->fpb, c->fqb, c->fwork);
-    launch_to_external<float, float>(c->g, c->fqb, (float*)d_y, c->s);
-  } else {
-    return fail(c, CSIPM_EINVAL, "precision");
-  }
+  if (precision == CSIPM_FP64) op_H<double>(c, (const double*)d_beta, (double*)d_y, c->work, true);
+  else if (precision == CSIPM_FP32) op_H<float>(c, (const float*)d_beta, (float*)d_y, c->fwork, true);
+  else return fail(c, CSIPM_EINVAL, "precision");
   return hip_check(c, "apply_H");
 }
 
 csipm_status csipm_apply_K(csipm_ctx* c, const void* d_pb, const void* d_pz, void* d_qb, void* d_qz, int precision) {
   if (!c || !d_pb || !d_pz || !d_qb || !d_qz) return CSIPM_EINVAL;
-  if (precision == CSIPM_FP64) {
-    launch_to_internal<double, double>(c->g, (const double*)d_pb, c->pb, c->s);
-    launch_to_internal<double, double>(c->g, (const double*)d_pz, c->pz, c->s);
-    op_K<double>(c, c->pb, c->pz, c->sig1, c->sig2, c->qb, c->qz, c->work, nullptr);
-    launch_to_external<double, double>(c->g, c->qb, (double*)d_qb, c->s);
-    launch_to_external<double, double>(c->g, c->qz, (double*)d_qz, c->s);
-  } else if (precision == CSIPM_FP32) {
-    launch_to_internal<float, float>(c->g, (const float*)d_pb, c->fpb, c->s);
-    launch_to_internal<float, float>(c->g, (const float*)d_pz, c->fpz, c->s);
-    op_K<float>(c, c->fpb, c->fpz, c->sig1f, c->sig2f, c->fqb, c->fqz, c->fwork, nullptr);
-    launch_to_external<float, float>(c->g, c->fqb, (float*)d_qb, c->s);
-    launch_to_external<float, float>(c->g, c->fqz, (float*)d_qz, c->s);
-  } else {
+  if (precision == CSIPM_FP64)
+    op_K<double>(c, (const double*)d_pb, (const double*)d_pz, c->sig1, c->sig2, (double*)d_qb, (double*)d_qz,
+                 c->work, nullptr, nullptr, true);
+  else if (precision == CSIPM_FP32)
+    op_K<float>(c, (const float*)d_pb, (const float*)d_pz, c->sig1f, c->sig2f, (float*)d_qb, (float*)d_qz, c->fwork,
+                nullptr, nullptr, true);
+  else
     return fail(c, CSIPM_EINVAL, "precision");
-  }
   return hip_check(c, "apply_K");
 }
 

@@ -132,19 +132,19 @@ struct Twiddles {
 };
 
 // An even N3 gives the half-spectrum layout (n = n1*n2*n3 reals = n1*n2*m
-// complex).  An odd N3 has no Nyquist plane to pack beside the DC plane, so
-// its beta-space vectors keep the external order, the transforms run on the
-// full Hermitian spectrum (n1*n2*n3 complex), and when n1*n2*n3 is odd one
-// more coordinate with no data (a zero column of A) makes the vector length
-// n even for the pairwise kernels; the LASSO sets it to 0.
+// complex).  An odd N3 has no Nyquist plane to pack beside the DC plane: its
+// beta-space vectors keep the external order, the transforms run on half
+// spectra of m = (n3 + 1) / 2 values (n1*n2*m complex), and when n1*n2*n3 is
+// odd one more coordinate with no data (a zero column of A) makes the vector
+// length n even for the pairwise kernels; the LASSO sets it to 0.
 struct Grid {
-  int n1, n2, n3, m;   // m = n3/2 (even N3)
+  int n1, n2, n3, m;   // m = n3/2, (n3+1)/2 for an odd n3
   long long n;         // beta-space length: nr, or nr + 1 when nr is odd
   long long nr;        // real-space samples n1*n2*n3
   bool odd3() const { return (n3 & 1) != 0; }
 };
 inline Grid make_grid(int n1, int n2, int n3) {
-  Grid g{n1, n2, n3, n3 / 2, 0, (long long)n1 * n2 * n3};
+  Grid g{n1, n2, n3, (n3 + 1) / 2, 0, (long long)n1 * n2 * n3};
   g.n = g.nr + (g.nr & 1);
   return g;
 }
@@ -268,10 +268,12 @@ __device__ __forceinline__ void p_block(T zb, T zz, T s1, T s2, double c, double
 // The axis-1 passes also map the m = 0 plane between the real
 // parametrisation and the spectrum (inverse: on input; forward: on output,
 // before the epilogue); the axis-1 inverse pass applies the direction update
-// ea->k.u when ea is set and ea->k.u.zb is not null.
+// ea->k.u when ea is set and ea->k.u.zb is not null.  ext: the beta-space
+// side of an axis-1 pass (the inverse pass's src; the forward pass's dst, or
+// p and q of EPI_K, without a direction update) is in the external layout.
 template <typename T>
 void launch_axis12(const Grid& g, int axis, int dir, const T* src, T* dst, const Twiddles<T>& tw,
-                   int epi, const EpiArgs<T>* ea, const int* skip, hipStream_t s);
+                   int epi, const EpiArgs<T>* ea, const int* skip, hipStream_t s, bool ext = false);
 template <typename T>
 void launch_axis3(const Grid& g, int mode, const T* src, T* dst, const uint32_t* maskbits,
                   const Twiddles<T>& tw, const int* skip, hipStream_t s);
@@ -281,44 +283,12 @@ void launch_axis3(const Grid& g, int mode, const T* src, T* dst, const uint32_t*
 int axis12_blocks(const Grid& g, int axis, int elem_bytes, int dir);
 // whether the FFT passes have kernels for extent N on `axis` (1, 2: pencils
 // of length N; 3: half length N/2 for an even N, full length for an odd N,
-// which takes the full-spectrum transforms): every N = 2^a 3^b 5^c 7^d in
+// whose rows are transformed two by two): every N = 2^a 3^b 5^c 7^d in
 // [3, 1024] (instantiated register-resident kernels for the powers of two
 // and the lengths fft_mixed_f64/f32.hip list, the in-place LDS kernels of
 // fft_any.h for the rest), and on axes 1 and 2 also 1 and 2 (2D and 1D
 // grids)
 bool fft_extent_supported(int N, int axis);
-
-// Full-spectrum transforms of a grid with an odd N3 (Grid::odd3): beta in
-// external order, work holds n1*n2*n3 complex values.  Each launch returns at
-// once when *skip is set.
-constexpr int kCpMaxBlocks = 1024;
-// workgroups (and partials) of cp_unmap
-int cp_blocks(const Grid& g);
-// work = B^H beta (the Hermitian spectrum of the real parametrisation)
-template <typename T>
-void cp_map(const Grid& g, const T* beta, T* work, const int* skip, hipStream_t s);
-// p <- z + beta p (both halves; the CG direction update before a K-apply)
-template <typename T>
-void cp_pupdate(const Grid& g, T* pb, T* pz, const T* zb, const T* zz, const double* beta, const int* skip,
-                hipStream_t s);
-// unnormalised complex FFT of work along axes 1, 2, 3 (dir +1: inverse,
-// exp(+); dir -1: forward, along 3, 2, 1)
-template <typename T>
-void cp_passes(const Grid& g, int dir, T* work, const Twiddles<T>& tw, const int* skip, hipStream_t s);
-// work = mask * Re(work) / nr (the normalisations of an inverse and a
-// forward unitary transform), imaginary part 0
-template <typename T>
-void cp_mask(const Grid& g, T* work, const uint32_t* bits, const int* skip, hipStream_t s);
-// x = Re(work) / sqrt(nr); work = x / sqrt(nr)
-template <typename T>
-void cp_real(const Grid& g, const T* work, T* x, hipStream_t s);
-template <typename T>
-void cp_cplx(const Grid& g, const T* x, T* work, hipStream_t s);
-// the real parametrisation of the spectrum in work: written to out
-// (EPI_NONE) or handed to the K / refinement epilogue of ea (EPI_K, EPI_R;
-// ea->k.u is ignored, cp_pupdate applies it); returns the partial count
-template <typename T>
-int cp_unmap(const Grid& g, const T* work, T* out, int epi, const EpiArgs<T>* ea, const int* skip, hipStream_t s);
 
 // message of the last failed context-free call on this thread (noalloc.hip)
 const char* noctx_last_error();

@@ -244,13 +244,15 @@ __global__ void __launch_bounds__(kMaxThreads)
 k_axis12_any(const cx<T>* src, cx<T>* dst, StridedGeom<T> geo, const cx<T>* __restrict__ tw, int m, Plane0 pl0,
              Epi epi, const int* skip, AnyPlan pl) {
   if (skip && *skip) return;
-  constexpr bool MIX = AX == 1;
+  constexpr bool MIX = AX == 1 && Epi::IO != IO_ODD;
   const int L = pl.L, TM = 1 << pl.tmlog;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<T>* const tile = reinterpret_cast<cx<T>*>(smem_raw);
   cx<T>* const twl = tile + (size_t)L * TM;
   const int p = threadIdx.x & (TM - 1), t = threadIdx.x >> pl.tmlog;
-  const Lane12 ln = lane12<AX, DIR>(p, TM, geo, m, pl0);
+  const Lane12 ln = lane12<AX, DIR, Epi::IO>(p, TM, geo, m, pl0);
+  XLane xl{};
+  if constexpr (Epi::IO != IO_INT) xl = xlane<Epi::IO>(ln, m, pl0.n2);
   cx<T>* const a = tile + p;
   for (int i = threadIdx.x; i < L; i += blockDim.x) twl[i] = tw[i];
   bool upd = false;
@@ -268,15 +270,14 @@ k_axis12_any(const cx<T>* src, cx<T>* dst, StridedGeom<T> geo, const cx<T>* __re
       cx<T> v[R];
 #pragma unroll
       for (int q = 0; q < R; ++q)
-        v[q] = load_input(src, ln.base + (long long)(j + q * nbf) * geo.estride, ln.active, upd, be, epi,
-                          MIX && ln.m0);
+        v[q] = read_input<T, DIR>(src, j + q * nbf, L, geo, ln, xl, pl0.n2, upd, be, epi, AX == 1 && ln.m0);
       if constexpr (MIX) {
         if (ln.m0 && ln.active) {
-          const long long prow = (long long)((pl0.n2 - ln.k2) % pl0.n2) * m;
+          const int prow = ln.k2 ? pl0.n2 - ln.k2 : 0;
 #pragma unroll
           for (int q = 0; q < R; ++q) {
             const int e = j + q * nbf;
-            const cx<T> y = load_input(src, prow + (long long)((L - e) % L) * geo.estride, true, upd, be, epi, true);
+            const cx<T> y = partner_value<T, DIR>(src, prow, e ? L - e : 0, geo, m, pl0.n2, epi, upd, be);
             v[q] = plane0_mix<T, DIR>(v[q], y, e, ln, L, pl0.n2);
           }
         }
@@ -305,17 +306,11 @@ k_axis12_any(const cx<T>* src, cx<T>* dst, StridedGeom<T> geo, const cx<T>* __re
       dft_r<R, DIR, T>(v);
       const int f = block_freq(b, pl);
 #pragma unroll
-      for (int q = 0; q < R; ++q) {
-        const int e = f + q * nbf;
-        cx<T> h = v[q];
-        if (plane0_keep<AX, DIR>(e, h, ln, L, pl0.n2)) {
-          const long long idx = ln.base + (long long)e * geo.estride;
-          if constexpr (Epi::NRED > 0) epi(idx, h, acc, MIX && ln.m0);
-          else dst[idx] = h;
-        }
-      }
+      for (int q = 0; q < R; ++q)
+        write_output<T, AX, DIR>(dst, f + q * nbf, v[q], L, geo, ln, xl, pl0.n2, epi, acc);
     }
   });
+  extra_output<T, DIR>(epi, acc);
   if constexpr (Epi::NRED > 0)
     block_sums_rt<Epi::NRED, Epi::NMAX>(acc, epi.partial, epi.pstride, reinterpret_cast<double*>(smem_raw));
 }
@@ -420,6 +415,116 @@ k_axis3_any(const cx<T>* src, cx<T>* dst, const uint32_t* __restrict__ mask, con
   }
 }
 
+// Axis-3 pass of an odd N3 = L: two real rows a and b share one complex
+// transform of length L, z = a + i b.  Its inverse starts from Z_e = A_e + i B_e
+// and Z_{L-e} = conj(A_e) + i conj(B_e) (e < M = (L + 1) / 2; the half spectra
+// carry the sqrt2 of the real parametrisation, the value of e = 0 does not
+// and is real), the mask acts on a and b, and the forward transform Y splits
+// into A_e = (Y_e + conj(Y_{L-e})) / 2 and B_e = (Y_e - conj(Y_{L-e})) / 2i.
+// A workgroup holds TM pairs: 2 TM rows, one run of memory on either side.
+// (Complex transforms of the whole Hermitian spectrum along all three axes,
+// with passes of their own for the map, the mask and the parametrisation,
+// moved twice the bytes: apply_At at 105 x 135 x 75 in FP64 69 us, now 33.)
+// Factors are left to the launch's scales as in k_axis3.
+template <typename T, int MODE>
+__global__ void __launch_bounds__(kMaxThreads)
+k_axis3_odd(const T* src_, T* dst_, const uint32_t* __restrict__ mask, const cx<T>* __restrict__ tw, int npencils,
+            T sc_c2r, T sc_dc, T sc_ac, const int* skip, AnyPlan pl) {
+  if (skip && *skip) return;
+  const int L = pl.L, TM = 1 << pl.tmlog, ES = TM + 1, M = (L + 1) / 2;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cx<T>* const tile = reinterpret_cast<cx<T>*>(smem_raw);
+  cx<T>* const twl = tile + (size_t)L * ES;
+  uint32_t* const mw = reinterpret_cast<uint32_t*>(twl + L);
+  const int p = threadIdx.x & (TM - 1), t = threadIdx.x >> pl.tmlog;
+  cx<T>* const a = tile + p;
+  for (int i = threadIdx.x; i < L; i += blockDim.x) twl[i] = tw[i];
+  const long long row0 = 2ll * blockIdx.x * TM;
+  const int nrow = (int)min((long long)2 * TM, npencils - row0);   // rows of this workgroup
+  const long long bit0 = row0 * L, word0 = bit0 >> 5;
+  if constexpr (MODE == A3_FULL) {
+    const int nw = (int)(((bit0 + (long long)nrow * L - 1) >> 5) - word0) + 1;
+    for (int i = threadIdx.x; i < nw; i += blockDim.x) mw[i] = mask[word0 + i];
+  }
+  if constexpr ((MODE & A3_C2R) != 0) {
+    const cx<T>* const src = reinterpret_cast<const cx<T>*>(src_) + row0 * M;
+    for (int i = threadIdx.x; i < TM * M; i += blockDim.x) {
+      const int pp = div_m(i, pl.hm), e = i - pp * M;
+      cx<T> x{T(0), T(0)}, y{T(0), T(0)};
+      if (2 * pp < nrow) x = src[2 * pp * M + e];
+      if (2 * pp + 1 < nrow) y = src[(2 * pp + 1) * M + e];
+      if (e == 0) {
+        const T s2 = T(1.41421356237309504880);
+        tile[pp] = {s2 * x.re, s2 * y.re};
+      } else {
+        tile[e * ES + pp] = {x.re - y.im, x.im + y.re};
+        tile[(L - e) * ES + pp] = {x.re + y.im, y.re - x.im};
+      }
+    }
+    stages<T, +1, false>(a, ES, pl, 0, pl.nst - 1, t, twl);
+    __syncthreads();
+    with_radix(pl.r[pl.nst - 1], [&](auto rc) {
+      constexpr int R = decltype(rc)::value;
+      const int nbf = L / R;
+      for (int b = t; b < nbf; b += pl.nt) {
+        cx<T>* const x = a + b * R * ES;
+        cx<T> v[R];
+#pragma unroll
+        for (int q = 0; q < R; ++q) v[q] = x[q * ES];
+        dft_r<R, +1, T>(v);
+        if constexpr (MODE == A3_FULL) {
+          const int off = (int)(bit0 & 31) + 2 * p * L + block_freq(b, pl);
+#pragma unroll
+          for (int q = 0; q < R; ++q) {
+            const int ba = off + q * nbf, bb = ba + L;
+            if (!(2 * p < nrow && ((mw[ba >> 5] >> (ba & 31)) & 1u))) v[q].re = T(0);
+            if (!(2 * p + 1 < nrow && ((mw[bb >> 5] >> (bb & 31)) & 1u))) v[q].im = T(0);
+          }
+          dft_r<R, -1, T>(v);
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q) x[q * ES] = v[q];
+      }
+    });
+    if constexpr (MODE == A3_C2R) {
+      __syncthreads();
+      for (int i = threadIdx.x; i < nrow * L; i += blockDim.x) {
+        const int r = div_m(i, pl.lm), e = i - r * L;
+        const cx<T> z = tile[slot_of(e, pl) * ES + (r >> 1)];
+        dst_[row0 * L + i] = ((r & 1) ? z.im : z.re) * sc_c2r;
+      }
+      return;
+    }
+    stages<T, -1, true>(a, ES, pl, 0, pl.nst - 1, t, twl);
+  } else {
+    const T* const src = src_ + row0 * L;
+    for (int i = threadIdx.x; i < TM * L; i += blockDim.x) {
+      const int pp = div_m(i, pl.lm), e = i - pp * L;
+      tile[slot_of(e, pl) * ES + pp] = {2 * pp < nrow ? src[2 * pp * L + e] : T(0),
+                                        2 * pp + 1 < nrow ? src[(2 * pp + 1) * L + e] : T(0)};
+    }
+    stages<T, -1, true>(a, ES, pl, 0, pl.nst, t, twl);
+  }
+  __syncthreads();
+  cx<T>* const dst = reinterpret_cast<cx<T>*>(dst_) + row0 * M;
+  for (int i = threadIdx.x; i < TM * M; i += blockDim.x) {
+    const int pp = div_m(i, pl.hm), e = i - pp * M;
+    if (2 * pp >= nrow) continue;
+    const cx<T> y = tile[e * ES + pp];
+    cx<T> x0, x1;
+    if (e == 0) {
+      x0 = {y.re * sc_dc, T(0)};
+      x1 = {y.im * sc_dc, T(0)};
+    } else {
+      const cx<T> z = tile[(L - e) * ES + pp];
+      x0 = cscale(cx<T>{y.re + z.re, y.im - z.im}, sc_ac);
+      x1 = cscale(cx<T>{y.im + z.im, z.re - y.re}, sc_ac);
+    }
+    dst[2 * pp * M + e] = x0;
+    if (2 * pp + 1 < nrow) dst[(2 * pp + 1) * M + e] = x1;
+  }
+}
+
 }  // namespace any
 
 template <typename T, int AX, int DIR, class Epi>
@@ -428,7 +533,7 @@ bool launch_axis12_any(int L, dim3 grid, const cx<T>* src, cx<T>* dst, StridedGe
   AnyPlan plan;
   if (!any_plan(L, (int)sizeof(cx<T>), plan)) return false;
   const int tm = 1 << plan.tmlog;
-  const Plane0 pl{n2, AX == 1 ? plane0_groups(DIR) : 0};
+  const Plane0 pl{n2, AX == 1 && Epi::IO != IO_ODD ? plane0_groups(DIR) : 0};
   const size_t shm = (size_t)(tm + 1) * L * sizeof(cx<T>);   // (the tile and the twiddles)
   auto kern = any::k_axis12_any<T, AX, DIR, Epi>;
   if (shm > 65536)
@@ -459,6 +564,25 @@ bool launch_axis3_any(int L, int mode, int np, const cx<T>* cs, cx<T>* cd, const
   return true;
 }
 
+template <typename T>
+bool launch_axis3_odd(int L, int mode, int np, const T* src, T* dst, const uint32_t* maskbits, const cx<T>* tw3,
+                      T sc_c2r, T sc_dc, T sc_ac, const int* skip, hipStream_t s) {
+  AnyPlan plan;
+  if (L % 2 == 0 || L < 3 || !any_plan(L, (int)sizeof(cx<T>), plan)) return false;
+  const int tm = 1 << plan.tmlog;
+  const size_t shm = (size_t)L * (tm + 2) * sizeof(cx<T>) + 4 * ((size_t)(2 * tm * L) / 32 + 2);
+  const dim3 grid((np + 2 * tm - 1) / (2 * tm)), block(tm * plan.nt);
+  auto go = [&](auto kern) {
+    if (shm > 65536)
+      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+    hipLaunchKernelGGL(kern, grid, block, shm, s, src, dst, maskbits, tw3, np, sc_c2r, sc_dc, sc_ac, skip, plan);
+  };
+  if (mode == A3_FULL) go(any::k_axis3_odd<T, A3_FULL>);
+  else if (mode == A3_C2R) go(any::k_axis3_odd<T, A3_C2R>);
+  else go(any::k_axis3_odd<T, A3_R2C>);
+  return true;
+}
+
 #define CSIPM_ANY12(T, AX, DIR, EPI)                                                                       \
   template bool launch_axis12_any<T, AX, DIR, EPI>(int, dim3, const cx<T>*, cx<T>*, StridedGeom<T>,        \
                                                    const cx<T>*, int, int, EPI, const int*, hipStream_t);
@@ -466,10 +590,18 @@ bool launch_axis3_any(int L, int mode, int np, const cx<T>* cs, cx<T>* cd, const
   CSIPM_ANY12(T, 1, +1, EpiP<T>)                                                                            \
   CSIPM_ANY12(T, 1, -1, EpiNone)                                                                            \
   CSIPM_ANY12(T, 1, -1, EpiK<T>)                                                                            \
+  CSIPM_ANY12(T, 1, +1, CSIPM_IO(EpiIn, T, IO_EXT))                                                         \
+  CSIPM_ANY12(T, 1, -1, CSIPM_IO(EpiOut, T, IO_EXT))                                                        \
+  CSIPM_ANY12(T, 1, -1, CSIPM_IO(EpiKX, T, IO_EXT))                                                         \
+  CSIPM_ANY12(T, 1, +1, CSIPM_IO(EpiIn, T, IO_ODD))                                                         \
+  CSIPM_ANY12(T, 1, -1, CSIPM_IO(EpiOut, T, IO_ODD))                                                        \
+  CSIPM_ANY12(T, 1, -1, CSIPM_IO(EpiKX, T, IO_ODD))                                                         \
   CSIPM_ANY12(T, 2, +1, EpiNone)                                                                            \
   CSIPM_ANY12(T, 2, -1, EpiNone)                                                                            \
   template bool launch_axis3_any<T>(int, int, int, const cx<T>*, cx<T>*, const uint32_t*, const cx<T>*,     \
-                                    const cx<T>*, T, T, T, const int*, hipStream_t);
+                                    const cx<T>*, T, T, T, const int*, hipStream_t);                       \
+  template bool launch_axis3_odd<T>(int, int, int, const T*, T*, const uint32_t*, const cx<T>*, T, T, T,   \
+                                    const int*, hipStream_t);
 
 }  // namespace fftk
 }  // namespace csipm

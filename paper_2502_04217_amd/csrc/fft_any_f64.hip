@@ -85,6 +85,7 @@ int any_tm(int w, int L) {
 
 CSIPM_ANY(double)
 CSIPM_ANY12(double, 1, -1, EpiR)
+CSIPM_ANY12(double, 1, -1, EpiRX)
 
 }  // namespace fftk
 }  // namespace csipm

@@ -329,12 +329,25 @@ __device__ __forceinline__ void block_sums_store(const double* v, double* out, i
 }
 
 // ------------------------------------------------------------ epilogues --
+// Where the beta-space side of an axis-1 pass lives (the inverse pass's
+// input, the forward pass's output and epilogue vectors):
+//   IO_INT  the internal layout (even N3);
+//   IO_EXT  the external beta layout, even N3: the operator applies read and
+//           write the caller's arrays themselves.  A conversion pass per array
+//           took 230 of the 431 us of an FP32 apply_K at 256^3 (now 246) and
+//           510 of 1270 at 300 x 400 x 400 (now 912): each element costs two
+//           scalar accesses, one of them on a reversed run, instead of one
+//           complex access and two more passes;
+//   IO_ODD  an odd N3, whose vectors keep the external order.
+enum BetaIO { IO_INT, IO_EXT, IO_ODD };
+
 // Applied to each output element h = (H p)[idx] of the last forward pass
 // (the m = 0 plane by the workgroups that unmix it).
 struct EpiNone {
   static constexpr int NRED = 0;
   static constexpr int NMAX = 0;
   static constexpr bool PRO = false;
+  static constexpr int IO = IO_INT;
   double* partial = nullptr;
   int pstride = 0;
 };
@@ -347,11 +360,91 @@ struct EpiP {
   static constexpr int NRED = 0;
   static constexpr int NMAX = 0;
   static constexpr bool PRO = true;
+  static constexpr int IO = IO_INT;
   cx<T>* p;
   const cx<T>* z;
   const double* beta;
   double* partial = nullptr;
   int pstride = 0;
+};
+
+// Input of the inverse pass from vectors in the external order (with EpiP's
+// update for IO_ODD).
+template <typename T, int IO_>
+struct EpiIn {
+  static constexpr int NRED = 0;
+  static constexpr int NMAX = 0;
+  static constexpr bool PRO = IO_ == IO_ODD;
+  static constexpr int IO = IO_;
+  const T* in;
+  T* p;
+  const T* z;
+  const double* beta;
+  double* partial = nullptr;
+  int pstride = 0;
+};
+
+// Output of the forward pass to a vector in the external order.  extra (IO_ODD):
+// the coordinate without data (-1: none), whose value is 0.
+template <typename T, int IO_>
+struct EpiOut {
+  static constexpr int NRED = 0;
+  static constexpr int NMAX = 0;
+  static constexpr bool PRO = false;
+  static constexpr int IO = IO_;
+  T* out;
+  long long extra;
+  double* partial = nullptr;
+  int pstride = 0;
+  // (idx: internal complex index; f, g: external indices of h.re and h.im;
+  // one: h.re alone)
+  __device__ __forceinline__ void operator()(long long, long long f, long long g, bool one, cx<T> h, double*,
+                                             bool) const {
+    out[f] = h.re;
+    if (!one) out[g] = h.im;
+  }
+};
+
+// EpiK on vectors in the external order (IO_EXT: the barrier diagonals stay
+// in the internal layout, and there is no direction update)
+template <typename T, int IO_>
+struct EpiKX {
+  static constexpr int NRED = 1;
+  static constexpr int NMAX = 0;
+  static constexpr bool PRO = false;
+  static constexpr int IO = IO_;
+  KArgs<T> a;
+  double* partial;
+  int pstride;
+  long long extra;
+  __device__ __forceinline__ void one_coord(long long f, T h, T s1, T s2, double* acc, bool m0) const {
+    T pb = a.pb[f], pz = a.pz[f];
+    if (IO_ == IO_ODD && a.u.zb) {
+      const T be = (T)*a.u.beta;
+      if (m0) {
+        pb = a.u.zb[f] + be * pb;
+        a.u.pb[f] = pb;
+      }
+      pz = a.u.zz[f] + be * pz;
+      a.u.pz[f] = pz;
+    }
+    T qb, qz;
+    k_block<T>(h, pb, pz, s1, s2, qb, qz);
+    a.qb[f] = qb;
+    a.qz[f] = qz;
+    acc[0] += (double)pb * (double)qb + (double)pz * (double)qz;
+  }
+  __device__ __forceinline__ void operator()(long long idx, long long f, long long g, bool one, cx<T> h, double* acc,
+                                             bool m0) const {
+    if constexpr (IO_ == IO_EXT) {
+      const cx<T> s1 = reinterpret_cast<const cx<T>*>(a.sig1)[idx], s2 = reinterpret_cast<const cx<T>*>(a.sig2)[idx];
+      one_coord(f, h.re, s1.re, s2.re, acc, m0);
+      one_coord(g, h.im, s1.im, s2.im, acc, m0);
+    } else {
+      one_coord(f, h.re, a.sig1[f], a.sig2[f], acc, m0);
+      if (!one) one_coord(g, h.im, a.sig1[g], a.sig2[g], acc, m0);
+    }
+  }
 };
 
 // q = K p (equation "condensedkkt" in Sigma form) and p.q
@@ -360,6 +453,7 @@ struct EpiK {
   static constexpr int NRED = 1;
   static constexpr int NMAX = 0;
   static constexpr bool PRO = false;
+  static constexpr int IO = IO_INT;
   KArgs<T> a;
   double* partial;
   int pstride;
@@ -399,6 +493,7 @@ struct EpiR {
   static constexpr int NRED = 2;
   static constexpr int NMAX = 1;
   static constexpr bool PRO = false;
+  static constexpr int IO = IO_INT;
   RArgs a;
   double* partial;
   int pstride;
@@ -420,6 +515,33 @@ struct EpiR {
       acc[0] += rb * zb + rz * zz;
       acc[1] = fmax(acc[1], fmax(fabs(rb), fabs(rz)));
     }
+  }
+};
+
+// EpiR on vectors in the external order (IO_ODD)
+struct EpiRX {
+  static constexpr int NRED = 2;
+  static constexpr int NMAX = 1;
+  static constexpr bool PRO = false;
+  static constexpr int IO = IO_ODD;
+  RArgs a;
+  double* partial;
+  int pstride;
+  long long extra;
+  __device__ __forceinline__ void one_coord(long long f, double h, double* acc) const {
+    const double g1 = a.sig1[f], g2 = a.sig2[f];
+    a.hd[f] = h;
+    double qb, qz, zb, zz;
+    k_block<double>(h, a.db[f], a.dz[f], g1, g2, qb, qz);
+    const double rb = a.hb[f] - qb, rz = a.hz[f] - qz;
+    pinv_block(rb, rz, g1, g2, a.c ? (double)a.c[f] : 1.0, zb, zz);
+    acc[0] += rb * zb + rz * zz;
+    acc[1] = fmax(acc[1], fmax(fabs(rb), fabs(rz)));
+  }
+  __device__ __forceinline__ void operator()(long long, long long f, long long g, bool one, cx<double> h, double* acc,
+                                             bool) const {
+    one_coord(f, h.re, acc);
+    if (!one) one_coord(g, h.im, acc);
   }
 };
 
@@ -530,7 +652,7 @@ struct Lane12 {
   bool canon;       // an m = 0 lane of a canonical row (or the even lane of a self-paired one)
   bool ded;         // the workgroup of the self-paired rows (forward axis-1 pass)
 };
-template <int AX, int DIR, typename T>
+template <int AX, int DIR, int IO, typename T>
 __device__ __forceinline__ Lane12 lane12(int p, int TM, const StridedGeom<T>& geo, int m, const Plane0& pl) {
   constexpr bool MIX = AX == 1;
   Lane12 ln;
@@ -552,11 +674,36 @@ __device__ __forceinline__ Lane12 lane12(int p, int TM, const StridedGeom<T>& ge
       ln.m0 = true;
       ln.k2 = qpen / m;
       ln.canon = 2 * ln.k2 < pl.n2;
-      if (DIR < 0 && self_paired_row(ln.k2, pl.n2)) ln.active = false;   // (taken by the first workgroup)
+      // (taken by the first workgroup)
+      if (IO != IO_ODD && DIR < 0 && self_paired_row(ln.k2, pl.n2)) ln.active = false;
     }
   }
   ln.base = ln.active ? (long long)(qpen / geo.inner) * geo.outer + (qpen % geo.inner) : 0;
   return ln;
+}
+
+// The external indices of an axis-1 lane's pencil: element e (k1 = e) at
+// r + e s, and its second part at i + e s, or i + ((L - e) mod L) s when rev:
+//   m >= 1: beta[k] and beta[-k];
+//   m = 0:  beta[k1, k2, 0] and beta[k1, k2, N3/2] (IO_EXT), or beta[k] and
+//           beta[-k] in the plane k3 = 0 (IO_ODD, which has no Nyquist plane).
+struct XLane {
+  long long r, i, s;
+  bool rev;
+  __device__ __forceinline__ long long f(int e) const { return r + e * s; }
+  __device__ __forceinline__ long long g(int e, int L) const { return i + (rev && e ? L - e : e) * s; }
+};
+template <int IO>
+__device__ __forceinline__ XLane xlane(const Lane12& ln, int m, int n2) {
+  const int n3 = IO == IO_EXT ? 2 * m : 2 * m - 1;
+  const int q = (int)ln.base, mm = ln.m0 ? 0 : q % m, k2 = q / m;   // (base is the pencil index on axis 1)
+  const long long row = (long long)k2 * n3, mrow = (long long)(k2 ? n2 - k2 : 0) * n3;
+  XLane x;
+  x.s = (long long)n2 * n3;
+  x.r = row + mm;
+  x.rev = IO == IO_ODD || mm > 0;
+  x.i = mm > 0 ? mrow + n3 - mm : (IO == IO_EXT ? row + m : mrow);
+  return x;
 }
 
 // The partner rows of the workgroup's m = 0 lanes, reversed (element e of
@@ -568,6 +715,24 @@ __device__ __forceinline__ Lane12 lane12(int p, int TM, const StridedGeom<T>& ge
 // in the forward pass's first workgroup lanes 0-3 are the slots (partner =
 // own row).  Returns the slot count (uniform over the workgroup; 0: no
 // m = 0 lane, nothing staged and no barrier) and the lane's slot.
+template <typename T, int DIR, class Epi>
+__device__ __forceinline__ cx<T> partner_value(const cx<T>* src, int prow, int e, const StridedGeom<T>& geo, int m,
+                                               int n2, const Epi& epi, bool upd, T be) {
+  if constexpr (DIR > 0 && Epi::IO == IO_EXT) {
+    const T* const x = epi.in + ((long long)e * n2 + prow) * (2 * m);
+    return {x[0], x[m]};
+  } else {
+    const long long i1 = (long long)prow * m + (long long)e * geo.estride;
+    cx<T> y = src[i1];
+    if constexpr (Epi::PRO) {
+      if (upd) {
+        const cx<T> zb = epi.z[i1];
+        y = {zb.re + be * y.re, zb.im + be * y.im};
+      }
+    }
+    return y;
+  }
+}
 template <typename T, int DIR, class Epi>
 __device__ __forceinline__ int stage_partners(cx<T>* lds, const cx<T>* src, int L, int TM, int nthr,
                                               const StridedGeom<T>& geo, int m, const Plane0& pl, const Epi& epi,
@@ -590,15 +755,7 @@ __device__ __forceinline__ int stage_partners(cx<T>* lds, const cx<T>* src, int 
     // was kept in scratch memory)
     if (row >= 0) {
       const int prow = ded ? row : (pl.n2 - row) % pl.n2;
-      const long long i1 = (long long)prow * m + (long long)((L - i) % L) * geo.estride;
-      cx<T> y = src[i1];
-      if constexpr (Epi::PRO) {
-        if (upd) {
-          const cx<T> zb = epi.z[i1];
-          y = {zb.re + be * y.re, zb.im + be * y.im};
-        }
-      }
-      lds[j] = y;
+      lds[j] = partner_value<T, DIR>(src, prow, (L - i) % L, geo, m, pl.n2, epi, upd, be);
     } else {
       lds[j] = cx<T>{T(0), T(0)};
     }
@@ -648,6 +805,65 @@ __device__ __forceinline__ cx<T> load_input(const cx<T>* src, long long idx, boo
   return x;
 }
 
+// Element e of a lane's pencil as the inverse pass reads it (any pass reads
+// its input through this; the forward passes and axis 2 read src).
+template <typename T, int DIR, class Epi>
+__device__ __forceinline__ cx<T> read_input(const cx<T>* src, int e, int L, const StridedGeom<T>& geo,
+                                            const Lane12& ln, const XLane& xl, int n2, bool upd, T be,
+                                            const Epi& epi, bool keep_p) {
+  if constexpr (DIR < 0 || Epi::IO == IO_INT) {
+    return load_input(src, ln.base + (long long)e * geo.estride, ln.active, upd, be, epi, keep_p);
+  } else {
+    if (!ln.active) return {T(0), T(0)};
+    const long long f = xl.f(e), g = xl.g(e, L);
+    T a = epi.in[f], b = epi.in[g];
+    if constexpr (Epi::IO == IO_ODD) {
+      if (upd) {
+        a = epi.z[f] + be * a;
+        b = epi.z[g] + be * b;
+        if (!keep_p) {
+          epi.p[f] = a;
+          epi.p[g] = b;
+        }
+      }
+      if (ln.m0) {   // the plane k3 = 0: the spectrum from beta[k] and beta[-k]
+        const T rs2 = T(0.70710678118654752440);
+        const int c = cls2(e, ln.k2, L, n2);
+        return c == 0 ? cx<T>{a, T(0)} : (c == 1 ? cx<T>{rs2 * a, rs2 * b} : cx<T>{rs2 * b, -rs2 * a});
+      }
+    }
+    return {a, b};
+  }
+}
+
+// Output element e of a lane's pencil: written, or handed to the epilogue.
+template <typename T, int AX, int DIR, class Epi>
+__device__ __forceinline__ void write_output(cx<T>* dst, int e, cx<T> h, int L, const StridedGeom<T>& geo,
+                                             const Lane12& ln, const XLane& xl, int n2, const Epi& epi, double* acc) {
+  const long long idx = ln.base + (long long)e * geo.estride;
+  if constexpr (DIR < 0 && Epi::IO == IO_ODD) {
+    if (ln.m0) {   // the real parametrisation of the plane k3 = 0
+      const T sq2 = T(1.41421356237309504880);
+      const int c = cls2(e, ln.k2, L, n2);
+      h = {c == 0 ? h.re : (c == 1 ? sq2 * h.re : -sq2 * h.im), T(0)};
+    }
+    epi(idx, xl.f(e), xl.g(e, L), ln.m0, h, acc, ln.m0);
+  } else if (plane0_keep<AX, DIR>(e, h, ln, L, n2)) {
+    if constexpr (DIR < 0 && Epi::IO == IO_EXT) epi(idx, xl.f(e), xl.g(e, L), false, h, acc, ln.m0);
+    else if constexpr (Epi::NRED > 0) epi(idx, h, acc, AX == 1 && ln.m0);
+    else dst[idx] = h;
+  }
+}
+
+// The coordinate without data of an odd grid: H is 0 there.
+template <typename T, int DIR, class Epi>
+__device__ __forceinline__ void extra_output(const Epi& epi, double* acc) {
+  if constexpr (DIR < 0 && Epi::IO == IO_ODD) {
+    if (epi.extra >= 0 && blockIdx.x == 0 && threadIdx.x == 0)
+      epi(0, epi.extra, epi.extra, true, cx<T>{T(0), T(0)}, acc, true);
+  }
+}
+
 template <typename T, int L, int AX, int DIR, class Epi>
 __global__ void __launch_bounds__((strided_threads<T, L, AX, DIR>()))
 k_axis12(const cx<T>* src, cx<T>* dst, StridedGeom<T> geo,
@@ -660,11 +876,14 @@ k_axis12(const cx<T>* src, cx<T>* dst, StridedGeom<T> geo,
   constexpr int SL = last_stage<L, E>();
   constexpr bool MIX = AX == 1;
   static_assert(!MIX || TM >= 4, "the self-paired rows take four lanes of one workgroup");
+  static_assert(Epi::IO != IO_ODD, "an odd N3 takes the axis-1 passes of fft_any.h");
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
   const int p = threadIdx.x % TM;
   const int t = threadIdx.x / TM;
-  const Lane12 ln = lane12<AX, DIR>(p, TM, geo, m, pl);
+  const Lane12 ln = lane12<AX, DIR, Epi::IO>(p, TM, geo, m, pl);
+  XLane xl{};
+  if constexpr (Epi::IO != IO_INT) xl = xlane<Epi::IO>(ln, m, pl.n2);
 
   cx<T> v[VM];
   bool upd = false;
@@ -674,7 +893,7 @@ k_axis12(const cx<T>* src, cx<T>* dst, StridedGeom<T> geo,
     if (upd) be = (T)*epi.beta;
   }
   for_stage_io<L, E, 0>(t, [&](int s, int e) {
-    v[s] = load_input(src, ln.base + (long long)e * geo.estride, ln.active, upd, be, epi, MIX && ln.m0);
+    v[s] = read_input<T, DIR>(src, e, L, geo, ln, xl, pl.n2, upd, be, epi, MIX && ln.m0);
   });
   // (the partner rows go to the tile's LDS, which the FFT stages do not use
   // before their first exchange, while the lanes' own loads are in flight)
@@ -690,26 +909,18 @@ k_axis12(const cx<T>* src, cx<T>* dst, StridedGeom<T> geo,
   auto lidx = [p](int e) { return e * TM + p; };
   fft_stages<T, L, E, DIR, 0>(v, t, lds, lidx, tw);
 
-  if constexpr (Epi::NRED > 0) {
-    double acc[Epi::NRED];
+  constexpr int NQ = Epi::NRED > 0 ? Epi::NRED : 1;
+  double acc[NQ];
 #pragma unroll
-    for (int q = 0; q < Epi::NRED; ++q) acc[q] = 0.0;
-    if (ln.active) {
-      for_stage_io<L, E, SL>(t, [&](int s, int e) {
-        cx<T> h = v[s];
-        if (plane0_keep<AX, DIR>(e, h, ln, L, pl.n2)) epi(ln.base + (long long)e * geo.estride, h, acc, MIX && ln.m0);
-      });
-    }
+  for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
+  if (ln.active) {
+    for_stage_io<L, E, SL>(t, [&](int s, int e) {
+      write_output<T, AX, DIR>(dst, e, v[s], L, geo, ln, xl, pl.n2, epi, acc);
+    });
+  }
+  if constexpr (Epi::NRED > 0)
     block_sums_store<TM * NT, Epi::NRED, Epi::NMAX>(acc, epi.partial, epi.pstride,
                                                     reinterpret_cast<double*>(smem_raw));
-  } else {
-    if (ln.active) {
-      for_stage_io<L, E, SL>(t, [&](int s, int e) {
-        cx<T> h = v[s];
-        if (plane0_keep<AX, DIR>(e, h, ln, L, pl.n2)) dst[ln.base + (long long)e * geo.estride] = h;
-      });
-    }
-  }
 }
 
 // workgroups in front of the tiles of an axis-1 pass (the forward pass's
@@ -1009,11 +1220,17 @@ template <typename T>
 bool launch_axis3_any(int L, int mode, int np, const cx<T>* cs, cx<T>* cd, const uint32_t* maskbits,
                       const cx<T>* twm, const cx<T>* tw3, T sc_c2r, T sc_dc, T sc_ac, const int* skip,
                       hipStream_t s);
+// The axis-3 pass of an odd N3 = L: pencils of M = (L + 1) / 2 values, no
+// Nyquist value, real rows of L (fft_any.h).
+template <typename T>
+bool launch_axis3_odd(int L, int mode, int np, const T* src, T* dst, const uint32_t* maskbits, const cx<T>* tw3,
+                      T sc_c2r, T sc_dc, T sc_ac, const int* skip, hipStream_t s);
 // pencils per workgroup of the strided pass that serves length L
 inline int pass_tm(int w, int L, int axis, int dir) {
   return templated12(L) ? strided_tm(w, L, axis, dir) : any_tm(w, L);
 }
 
+#define CSIPM_IO(EPI, T, IO) EPI<T, IO>   // (a comma inside a macro argument)
 // The instances used: PREFIX is empty where they are compiled and `extern`
 // where they are only called.
 #define CSIPM_MIXED_INST12(PREFIX, T, AX, DIR, EPI)                                                           \
@@ -1023,6 +1240,9 @@ inline int pass_tm(int w, int L, int axis, int dir) {
   CSIPM_MIXED_INST12(PREFIX, T, 1, +1, EpiP<T>)                                                            \
   CSIPM_MIXED_INST12(PREFIX, T, 1, -1, EpiNone)                                                            \
   CSIPM_MIXED_INST12(PREFIX, T, 1, -1, EpiK<T>)                                                            \
+  CSIPM_MIXED_INST12(PREFIX, T, 1, +1, CSIPM_IO(EpiIn, T, IO_EXT))                                         \
+  CSIPM_MIXED_INST12(PREFIX, T, 1, -1, CSIPM_IO(EpiOut, T, IO_EXT))                                        \
+  CSIPM_MIXED_INST12(PREFIX, T, 1, -1, CSIPM_IO(EpiKX, T, IO_EXT))                                         \
   CSIPM_MIXED_INST12(PREFIX, T, 2, +1, EpiNone)                                                            \
   CSIPM_MIXED_INST12(PREFIX, T, 2, -1, EpiNone)                                                            \
   PREFIX template bool launch_axis3_mixed<T>(int, int, int, const cx<T>*, cx<T>*, const uint32_t*, const cx<T>*, \

@@ -28,7 +28,8 @@
 // These passes are bound by memory and the latency of its pipeline: the
 // transform costs two or three LDS round trips per element (five or six in
 // an axis-3 pass), and a run of TM pencils is one 128-byte line, so that no
-// two workgroups share the lines of an aligned row.  Against passes that kept
+// two workgroups share the lines of an aligned row (xcd_tile: nor two XCDs those
+// of any other).  Against passes that kept
 // the pencil in LDS through Stockham stages of radix 8, 4, 2, 3, 5, 7 (two
 // barriers per stage, 64-byte runs at these lengths), a K-apply takes, in us:
 //   300 x 400 x 400 FP32  1224 -> 705 (2.9 GB: 4.1 TB/s)
@@ -332,8 +333,9 @@ k_axis3_any(const cx<T>* src, cx<T>* dst, const uint32_t* __restrict__ mask, con
   const int p = threadIdx.x & (TM - 1), t = threadIdx.x >> pl.tmlog;
   cx<T>* const a = tile + p;
   for (int i = threadIdx.x; i < L; i += blockDim.x) twl[i] = twm[i];
-  const long long run = (long long)blockIdx.x * TM * L;
-  const int np = min(TM, npencils - (int)blockIdx.x * TM);   // pencils of this workgroup
+  const int tl = xcd_tile(blockIdx.x, gridDim.x);
+  const long long run = (long long)tl * TM * L;
+  const int np = min(TM, npencils - tl * TM);   // pencils of this workgroup
   const long long bit0 = 2 * run, word0 = bit0 >> 5;
   if constexpr (MODE == A3_FULL) {
     // the mask words of the run (bits bit0 .. bit0 + 2 np L)
@@ -439,7 +441,7 @@ k_axis3_odd(const T* src_, T* dst_, const uint32_t* __restrict__ mask, const cx<
   const int p = threadIdx.x & (TM - 1), t = threadIdx.x >> pl.tmlog;
   cx<T>* const a = tile + p;
   for (int i = threadIdx.x; i < L; i += blockDim.x) twl[i] = tw[i];
-  const long long row0 = 2ll * blockIdx.x * TM;
+  const long long row0 = 2ll * xcd_tile(blockIdx.x, gridDim.x) * TM;
   const int nrow = (int)min((long long)2 * TM, npencils - row0);   // rows of this workgroup
   const long long bit0 = row0 * L, word0 = bit0 >> 5;
   if constexpr (MODE == A3_FULL) {

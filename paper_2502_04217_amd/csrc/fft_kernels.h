@@ -642,6 +642,23 @@ struct Plane0 {
   int ndedicated;   // workgroups in front of the tiles (forward axis-1 pass: 1)
 };
 
+// The tile that workgroup b of n takes.  Workgroups go to the 8 XCDs in turn,
+// each with its own L2: each XCD takes one contiguous range of the tiles, so
+// that the lines two neighbouring tiles share (rows that do not start on a
+// line, and the reversed runs of the external layout) are fetched and written
+// through one L2, and an XCD's rows stay within few pages.  Tiles in launch
+// order against this: apply_K in FP32 at 300 x 400 x 400 912 and 780 us, at
+// 512^3 2561 and 2136; the FP64 axis-1 inverse pass at 512^3 563 and 491 us,
+// its axis-2 passes 409 and 366; at 256^3, which the last-level cache holds,
+// no difference beyond that of two runs.
+__device__ __forceinline__ int xcd_tile(int b, int n) {
+  const int q = n >> 3, r = n & 7, x = b & 7;
+  return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + (b >> 3);
+}
+__device__ __forceinline__ int strided_tile(const Plane0& pl) {
+  return xcd_tile((int)blockIdx.x - pl.ndedicated, (int)gridDim.x - pl.ndedicated);
+}
+
 // The pencil a lane of a strided pass transforms (pencil p of the
 // workgroup's TM) and its part in the m = 0 plane (axis 1).
 struct Lane12 {
@@ -668,7 +685,7 @@ __device__ __forceinline__ Lane12 lane12(int p, int TM, const StridedGeom<T>& ge
     ln.canon = (p & 1) == 0;
     qpen = ln.active ? ln.k2 * m : 0;
   } else {
-    qpen = ((int)blockIdx.x - (MIX ? pl.ndedicated : 0)) * TM + p;
+    qpen = strided_tile(pl) * TM + p;
     ln.active = qpen < geo.batch;
     if (MIX && ln.active && qpen % m == 0) {
       ln.m0 = true;
@@ -737,7 +754,7 @@ template <typename T, int DIR, class Epi>
 __device__ __forceinline__ int stage_partners(cx<T>* lds, const cx<T>* src, int L, int TM, int nthr,
                                               const StridedGeom<T>& geo, int m, const Plane0& pl, const Epi& epi,
                                               bool upd, T be, bool ded, int p, int& slot) {
-  const int q0 = ded ? 0 : ((int)blockIdx.x - pl.ndedicated) * TM;
+  const int q0 = ded ? 0 : strided_tile(pl) * TM;
   const int first = ded ? 0 : (q0 + m - 1) / m;
   const int nslot = ded ? 4 : (q0 + TM - 1) / m + 1 - first;
   slot = ded ? p : (q0 + p) / m - first;

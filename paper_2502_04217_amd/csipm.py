@@ -181,7 +181,7 @@ def small_workspace_bytes(shape, count: int) -> int:
 def solve_small_batch(signals, observed, lambdas=None, lambda_frac: float = 0.05, opts: Options | None = None,
                       **kw):
     """csipm_solve_small_batch: count problems of one small grid (each
-    extent <= 64) solved by one kernel, one workgroup per problem.
+    extent <= 64) solved by one kernel, a workgroup or a team per problem.
     signals: [count, N1, N2, N3] float64, observed: the same shape, nonzero =
     observed (numpy or torch); lambdas: [count] or None (lambda_frac times
     ||M_perp^T b||_inf).  Returns (beta [count, N1, N2, N3] float64 on the

@@ -1,15 +1,14 @@
-// Batches of small problems, one workgroup per problem (small.hip).
+// Batches of small problems, a workgroup or a team per problem (small.hip).
 #pragma once
 
 #include "csipm_internal.h"
 
 namespace csipm {
 
-// the largest extent of a small problem (direct DFTs: L^2 work per pencil)
+// the largest extent of a small problem
 constexpr int kSmallMaxExtent = 64;
-// the spectrum buffers (one, or two when an extent takes the direct DFT) of
-// a grid sit in LDS when they take at most this many bytes
-constexpr long long kSmallLdsBytes = 131072;
+// the most problems of a batch whose workgroups form teams
+constexpr int kSmallTeams = 128;
 
 // the options the small solver reads (those of csipm_options it uses)
 struct SmallOpts {
@@ -23,12 +22,25 @@ struct SmallOpts {
 };
 
 bool small_supported(int n1, int n2, int n3);
+// workspace bytes in front of the problems: the twiddle tables and the team
+// counters
+size_t small_front_bytes(int n1, int n2, int n3);
 // workspace bytes of one problem (a multiple of 256)
 size_t small_problem_bytes(int n1, int n2, int n3);
-// one launch of count workgroups; tw holds the tables exp(-2 pi i q / L) of
-// L = n1, n2, n3 in that order
+// one launch of a workgroup (or a team) per problem; tw holds the tables
+// exp(-2 pi i q / L) of L = n1, n2, n3 in that order, counters kSmallTeams
+// zeros 64 bytes apart
 hipError_t small_launch(int n1, int n2, int n3, int count, const double* signals, const uint8_t* observed,
                         const double* lambdas, double lambda_frac, double* beta_out, double* info, char* ws,
-                        const cx<double>* tw, const SmallOpts& o, hipStream_t s);
+                        const cx<double>* tw, unsigned* counters, const SmallOpts& o, hipStream_t s);
+
+// The grids that small_tiny.hip solves: at most 400 points, or kTinyMax with
+// extents 1, 2, 4, 8 and 16 only.
+constexpr int kTinyMax = 1024;
+bool tiny_grid(int n1, int n2, int n3);
+size_t tiny_problem_bytes(int n1, int n2, int n3);
+hipError_t tiny_launch(int n1, int n2, int n3, int count, const double* signals, const uint8_t* observed,
+                       const double* lambdas, double lambda_frac, double* beta_out, double* info, char* ws,
+                       const cx<double>* tw, const SmallOpts& o, hipStream_t s);
 
 }  // namespace csipm

@@ -6,19 +6,41 @@
 // batch needs no host round trip until it is done.
 //
 // The steps are those of the library's standard form in FP64 (the readings
-// of the barrier strategy, right-hand side and stopping rules), on the
-// simplest data path: H beta is recomputed by a full H-apply at every
-// iterate, and the operators run on the whole Hermitian spectrum, one axis
-// at a time, in place: a pencil of power-of-two length up to 32 is
-// transformed by one thread in registers (radix 2), any other length up to
-// kSmallMaxExtent by direct DFTs (L^2 work per pencil) through a second
-// buffer.  The spectrum sits in LDS when it fits (kSmallLdsBytes), else in
-// the problem's workspace.  A problem's result does not depend on the
-// others in the batch: a batch of one gives the same bits.
+// of the barrier strategy, right-hand side and stopping rules); H beta is
+// recomputed by a full H-apply at every iterate.
+//
+// An H-apply works on the half spectrum W[k1][k2][m], m <= N3 / 2, in LDS
+// (row stride MS, odd: consecutive rows start on different banks).  All
+// stages of all axes run in place over the whole tile, a butterfly per
+// thread and round: decimation in frequency on the way to real space, which
+// leaves each axis in digit-reversed slots, and decimation in time, which
+// starts from them, on the way back, so nothing is ever reordered (fft_any.h
+// states the two).  Two rows g and g + HR share one complex transform along
+// axis 3: Z_e = A_e + i B_e takes A's slot e and Z_{N3-e} = conj A_e +
+// i conj B_e B's slot e, so packing and unpacking are in place too.  Radices
+// up to 8; a prime factor above 8 is one stage of direct sums.
+// A grid whose tile exceeds kResident keeps W in the workspace, takes it
+// through LDS in tiles of axis-1 columns and of (k2, m) planes, and is solved by
+// a team of workgroups (below), which share the tiles and the vectors.
+//
+// What bounds it: for a resident grid the chain of stages (12 at 16^3, a
+// barrier each, 2-3 thousand cycles) and the passes over the vectors at the 28
+// bytes per cycle that one compute unit reaches; for a team that rate times its
+// workgroups, and its four barriers per Krylov step (6.8 us each).  Against
+// complex transforms of the whole spectrum, a pencil per thread in registers
+// (2 to 32 points) or direct DFTs in the workspace, one workgroup per problem,
+// a batch takes, in ms: 64 of 16^3 2.6 -> 2.0; 32 of 48 x 40 x 36 397 -> 8.8;
+// 64 of 32^3 29.6 -> 8.7; 16 of 64^3 about 500 -> 16; 50 of 24^3 38 -> 4.8.
+// Sixteen waves of 128 registers instead of eight of 232 spill and lose a
+// quarter.  A problem's result does not depend on the others in the batch: a
+// batch of one gives the same bits.
 #include "small.h"
+
+#include "fft_any.h"
 
 #include "../../include/csipm.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <string>
@@ -28,405 +50,994 @@ namespace csipm {
 
 namespace {
 
-constexpr int kSmallThreads = 512;
-constexpr int kSmallWaves = kSmallThreads / 64;
+using fftk::any::dft_r;
 
-struct SmallDims {
-  int n1, n2, n3;
-  long long n;
+constexpr int kMaxThreads = 512;
+constexpr int kMaxWaves = kMaxThreads / 64;
+// complex values of LDS tile at most (150 KB)
+constexpr int kTile = 9600;
+// largest tile that a grid is solved in by one workgroup
+constexpr int kResident = 4800;
+// outputs per thread and round in a stage of direct sums
+constexpr int kDirect = 4;
+// Fixed parts of every tile loop and sum over a grid that is not in LDS
+// (Plan::parts, at most kParts), and so the most workgroups of a team: 8, and
+// 16 from kLarge points.  With 16 everywhere the sums' barriers and the smaller
+// tiles cost a team of 8 more than a tenth (32 problems of 48 x 40 x 36: 10.3
+// against 9.2 ms); with 8 everywhere 16 problems of 64^3 leave half of the
+// compute units idle (22.7 against 16.2 ms).
+constexpr int kParts = 16, kLarge = 131072;
+
+// n / d by multiplication, n d < 2^32
+struct Div {
+  int d;
+  unsigned m;
+  __device__ __forceinline__ int operator()(int n) const { return d == 1 ? n : (int)__umulhi((unsigned)n, m); }
 };
+Div make_div(int d) { return Div{d, d > 1 ? (unsigned)((0x100000000ull + d - 1) / d) : 0u}; }
+
+constexpr int kStages = 6;
+struct Axis {
+  int L, nst;
+  int r[kStages], step[kStages];
+  Div ms[kStages];   // stride of a butterfly's values, B_s / R_s
+};
+struct Plan {
+  Axis ax[3];
+  int n1, n2, n3, M, MS, n;
+  int resident;      // the whole half spectrum in one LDS tile
+  int cols, planes;  // else: axis-1 columns and planes per tile
+  int tile;          // LDS tile (complex values)
+  int threads, parts;
+  Div dM, dMS, dn2, dn3, dcols;
+  Div dH[2], dplane[2];   // row pairs and (plane, m) pencils of a tile: all but the last, the last
+  Div dcw;                // threads side by side on a tile's columns
+  int cgroups;            // groups of them
+};
+
+// The plan, read where it is used: behind this the compiler cannot hoist the
+// scalar loads of its fields (nor the array bases) to the top of the solver,
+// where the 104 scalar registers would spill three times over and every use
+// would read a vector lane.
+__device__ __forceinline__ const Plan& fresh(uint64_t kernarg) {
+  asm volatile("" : "+s"(kernarg));
+  return *(const Plan*)(const __attribute__((address_space(4))) Plan*)kernarg;
+}
 
 // ------------------------------------------------------- block reductions --
-// (every thread of the workgroup calls these; red holds kSmallWaves doubles)
-// op 0: sum, 1: max, 2: min; the waves' values combined in wave order
-__device__ double block_reduce(double v, int op, double* red) {
-  v = op == 0 ? wave_sum(v) : op == 1 ? wave_max(v) : wave_min(v);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+// Sums, maxima and minima over the workgroup (every thread calls this and
+// gets the result; red holds NQ kMaxWaves doubles): within the waves, then
+// over the waves' values by the same exchange.
+// op 0: sum, 1: max, 2: min
+__device__ __forceinline__ double combine(int op, double a, double b) {
+  return op == 0 ? a + b : op == 1 ? fmax(a, b) : fmin(a, b);
+}
+template <int NQ>
+__device__ __forceinline__ void block_reduce(double* v, const int* op, double* red) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) v[q] = combine(op[q], v[q], __shfl_xor(v[q], o, 64));
   __syncthreads();
-  if (lane == 0) red[wv] = v;
+  if (lane == 0)
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) red[q * kMaxWaves + wv] = v[q];
   __syncthreads();
-  double a = red[0];
-  for (int k = 1; k < kSmallWaves; ++k) a = op == 0 ? a + red[k] : op == 1 ? fmax(a, red[k]) : fmin(a, red[k]);
-  return a;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) v[q] = red[q * kMaxWaves + (lane & (nw - 1))];   // (nw is a power of two)
+  for (int o = nw >> 1; o > 0; o >>= 1)
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) v[q] = combine(op[q], v[q], __shfl_xor(v[q], o, 64));
 }
 
-// ------------------------------------------------------------- transforms --
-__device__ __forceinline__ void unravel(long long f, const SmallDims& d, int& k1, int& k2, int& k3) {
-  k3 = (int)(f % d.n3);
-  const long long r = f / d.n3;
-  k2 = (int)(r % d.n2);
-  k1 = (int)(r / d.n2);
-}
-__device__ __forceinline__ long long mirror_of(int k1, int k2, int k3, const SmallDims& d) {
-  const int m1 = k1 ? d.n1 - k1 : 0, m2 = k2 ? d.n2 - k2 : 0, m3 = k3 ? d.n3 - k3 : 0;
-  return ((long long)m1 * d.n2 + m2) * d.n3 + m3;
-}
-
-// One direct DFT pass along `axis` (1, 2, 3) from src to dst: dst[.., k, ..]
-// = sum_j src[.., j, ..] exp(dir 2 pi i j k / L), the sum taken in order j =
-// 0, 1, ..., L - 1 with tw[q] = exp(-2 pi i q / L) from the host tables.
-__device__ void dft_pass(const cx<double>* src, cx<double>* dst, const SmallDims& d, int axis, int dir,
-                         const cx<double>* tw) {
-  const int L = axis == 1 ? d.n1 : axis == 2 ? d.n2 : d.n3;
-  const long long st = axis == 1 ? (long long)d.n2 * d.n3 : axis == 2 ? d.n3 : 1;
-  for (long long f = threadIdx.x; f < d.n; f += kSmallThreads) {
-    int k1, k2, k3;
-    unravel(f, d, k1, k2, k3);
-    const int k = axis == 1 ? k1 : axis == 2 ? k2 : k3;
-    const long long base = f - (long long)k * st;
-    double re = 0.0, im = 0.0;
-    int q = 0;   // j k mod L
-    for (int j = 0; j < L; ++j) {
-      const cx<double> x = src[base + (long long)j * st];
-      const cx<double> w = tw[q];
-      const double wi = dir > 0 ? -w.im : w.im;
-      re += x.re * w.re - x.im * wi;
-      im += x.re * wi + x.im * w.re;
-      q += k;
-      if (q >= L) q -= L;
+// ------------------------------------------------------------------ teams --
+// The G workgroups of a problem (one for a resident grid).  All of them take
+// every decision from the same values: a sum is made of kParts parts, part p by
+// workgroup p mod G, combined in order by each, so the bits do not depend on
+// G.  The launch makes sure that all workgroups are resident, and their
+// barrier gives up after kSpinTicks.
+constexpr long long kSpinTicks = 500000000ll;   // 5 s of the 100 MHz clock
+constexpr unsigned kAbort = 0x40000000u;
+struct Team {
+  int G, rank;
+  unsigned target;   // arrivals the next barrier waits for
+  unsigned* count;   // arrivals so far (device memory, 0 at launch)
+  double* parts;     // [2][kParts][5] partial sums, used in turn
+  int turn;
+  int* bad;          // LDS: the barrier gave up
+};
+__device__ __forceinline__ void team_sync(Team& t) {
+  __syncthreads();
+  if (t.G == 1) return;
+  t.target += t.G;
+  if (threadIdx.x == 0) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __hip_atomic_fetch_add(t.count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const long long t0 = wall_clock64();
+    unsigned n;
+    while ((n = __hip_atomic_load(t.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < t.target) {
+      __builtin_amdgcn_s_sleep(1);
+      if (wall_clock64() - t0 > kSpinTicks) {
+        __hip_atomic_fetch_or(t.count, kAbort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        n = kAbort;
+        break;
+      }
     }
-    dst[f] = {re, im};
+    if (n >= kAbort) *t.bad = 1;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   }
   __syncthreads();
 }
 
-constexpr int bitrev(int j, int L) {
-  int r = 0;
-  for (int b = 1; b < L; b <<= 1) {
-    r = (r << 1) | (j & 1);
-    j >>= 1;
-  }
-  return r;
-}
-
-// pencils of length L (a power of two) transformed in place, one per
-// thread: loaded in bit-reversed order, radix-2 butterflies in registers
-// (span len, twiddles tw[k L / len]), written back in order
-template <int L>
-__device__ void reg_pass(cx<double>* w, const SmallDims& d, int axis, int dir, const cx<double>* tw) {
-  const long long st = axis == 1 ? (long long)d.n2 * d.n3 : axis == 2 ? d.n3 : 1;
-  const long long npen = d.n / L;
-  for (long long P = threadIdx.x; P < npen; P += kSmallThreads) {
-    const long long base =
-        axis == 1 ? P : axis == 2 ? (P / d.n3) * ((long long)d.n2 * d.n3) + P % d.n3 : P * (long long)d.n3;
-    cx<double> v[L];
-#pragma unroll
-    for (int j = 0; j < L; ++j) v[bitrev(j, L)] = w[base + (long long)j * st];
-#pragma unroll
-    for (int len = 2; len <= L; len <<= 1) {
-      const int half = len >> 1, step = L / len;
-#pragma unroll
-      for (int i = 0; i < L; i += len)
-#pragma unroll
-        for (int k = 0; k < half; ++k) {
-          const cx<double> t0 = tw[k * step];
-          const double wr = t0.re, wi = dir > 0 ? -t0.im : t0.im;
-          const cx<double> a = v[i + k], b = v[i + k + half];
-          const double tr = b.re * wr - b.im * wi, ti = b.re * wi + b.im * wr;
-          v[i + k] = {a.re + tr, a.im + ti};
-          v[i + k + half] = {a.re - tr, a.im - ti};
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < L; ++j) w[base + (long long)j * st] = v[j];
-  }
-  __syncthreads();
-}
-
-// whether an extent takes the register pass (else the direct DFT)
-__host__ __device__ constexpr bool reg_length(int L) { return L == 2 || L == 4 || L == 8 || L == 16 || L == 32; }
-
-// one axis of the full-spectrum transform of w, in place (scr: n complex of
-// scratch for the direct DFT of other lengths).  RMAX is the longest
-// register pencil the kernel instance holds (32 takes about twice the
-// registers of 16, so grids without a 32-point axis use the 16 instance).
-template <int RMAX>
-__device__ void axis_pass(cx<double>* w, cx<double>* scr, const SmallDims& d, int axis, int dir,
-                          const cx<double>* tw) {
-  const int L = axis == 1 ? d.n1 : axis == 2 ? d.n2 : d.n3;
-  if constexpr (RMAX >= 32) {
-    if (L == 32) {
-      reg_pass<32>(w, d, axis, dir, tw);
-      return;
-    }
-  }
-  switch (L) {
-    case 1:
-      return;
-    case 2:
-      reg_pass<2>(w, d, axis, dir, tw);
-      return;
-    case 4:
-      reg_pass<4>(w, d, axis, dir, tw);
-      return;
-    case 8:
-      reg_pass<8>(w, d, axis, dir, tw);
-      return;
-    case 16:
-      reg_pass<16>(w, d, axis, dir, tw);
-      return;
-    default:
-      dft_pass(w, scr, d, axis, dir, tw);
-      for (long long f = threadIdx.x; f < d.n; f += kSmallThreads) w[f] = scr[f];
-      __syncthreads();
-      return;
+// ----------------------------------------------------------------- stages --
+// Calls f(std::integral_constant<int, R>) for the runtime radix r <= 8 (an
+// FP64 radix-10 butterfly does not fit the 128 registers of a workgroup of
+// 1024 threads beside the solver's state).
+constexpr int kMaxRadix = 8;
+template <class F>
+__device__ __forceinline__ void with_radix(int r, F f) {
+  switch (r) {
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    case 7: f(std::integral_constant<int, 7>{}); break;
+    default: f(std::integral_constant<int, 8>{}); break;
   }
 }
 
-struct SmallTw {
-  const cx<double>* t1;
-  const cx<double>* t2;
-  const cx<double>* t3;
+// Pencils of a tile: pencil b is (b / inner, b % inner), element e of it at
+// (b / inner) outer + b % inner + e es.
+struct Lin {
+  Div inner;
+  int outer, es;
+  __device__ __forceinline__ int base(int b) const {
+    const int q = inner(b);
+    return q * outer + (b - q * inner.d);
+  }
+  __device__ __forceinline__ int first(int base, int e) const { return base + e * es; }
+  __device__ __forceinline__ int next(int at, int, int, int q, int ms) const { return at + q * ms * es; }
+  __device__ __forceinline__ int at(int base, int e) const { return base + e * es; }
+};
+// The row pairs of the axis-3 transform: element e < M in row g, else in row
+// g + H at N3 - e.
+struct Rows {
+  int MS, M, L, H;
+  __device__ __forceinline__ int base(int b) const { return b * MS; }
+  __device__ __forceinline__ int first(int base, int e) const { return at(base, e); }
+  __device__ __forceinline__ int next(int, int base, int e, int q, int ms) const { return at(base, e + q * ms); }
+  __device__ __forceinline__ int at(int base, int e) const { return e < M ? base + e : base + H * MS + (L - e); }
 };
 
-// y = H beta = A^T D A beta (beta and y in the external parametrisation of
-// derivation "map"); w0 holds the n-point spectrum, scr n complex of scratch.
-template <int RMAX>
-__device__ void h_apply(const double* beta, double* y, const uint8_t* obs, const SmallDims& d, const SmallTw& tw,
-                        cx<double>* w0, cx<double>* scr) {
-  const double rs2 = 0.70710678118654752440, sq2 = 1.41421356237309504880;
-  for (long long f = threadIdx.x; f < d.n; f += kSmallThreads) {
-    int k1, k2, k3;
-    unravel(f, d, k1, k2, k3);
-    const int c = cls3(k1, k2, k3, d.n1, d.n2, d.n3);
-    const double b = beta[f];
-    if (c == 0) {
-      w0[f] = {b, 0.0};
-    } else {
-      const double bm = beta[mirror_of(k1, k2, k3, d)];
-      w0[f] = c == 1 ? cx<double>{rs2 * b, rs2 * bm} : cx<double>{rs2 * bm, -rs2 * b};
-    }
-  }
-  __syncthreads();
-  axis_pass<RMAX>(w0, scr, d, 1, +1, tw.t1);
-  axis_pass<RMAX>(w0, scr, d, 2, +1, tw.t2);
-  axis_pass<RMAX>(w0, scr, d, 3, +1, tw.t3);
-  const double sc = 1.0 / (double)d.n;   // both unitary normalisations
-  for (long long f = threadIdx.x; f < d.n; f += kSmallThreads) w0[f] = {obs[f] ? w0[f].re * sc : 0.0, 0.0};
-  __syncthreads();
-  axis_pass<RMAX>(w0, scr, d, 3, -1, tw.t3);
-  axis_pass<RMAX>(w0, scr, d, 2, -1, tw.t2);
-  axis_pass<RMAX>(w0, scr, d, 1, -1, tw.t1);
-  for (long long f = threadIdx.x; f < d.n; f += kSmallThreads) {
-    int k1, k2, k3;
-    unravel(f, d, k1, k2, k3);
-    const int c = cls3(k1, k2, k3, d.n1, d.n2, d.n3);
-    const cx<double> h = w0[f];
-    y[f] = c == 0 ? h.re : (c == 1 ? sq2 * h.re : -sq2 * h.im);
-  }
-  __syncthreads();
+__device__ __forceinline__ cx<double> tw_of(const cx<double>* tw, int i, int sgn) {
+  cx<double> w = tw[i];
+  if (sgn > 0) w.im = -w.im;
+  return w;
 }
 
-// xi = A^T b_hat = B DFT(b_hat) (the adjoint of A, reading "adjoint")
-template <int RMAX>
-__device__ void at_apply(const double* x, const uint8_t* obs, double* out, const SmallDims& d, const SmallTw& tw,
-                         cx<double>* w0, cx<double>* scr) {
-  const double sq2 = 1.41421356237309504880;
-  const double sc = 1.0 / sqrt((double)d.n);
-  for (long long f = threadIdx.x; f < d.n; f += kSmallThreads) w0[f] = {obs[f] ? x[f] * sc : 0.0, 0.0};
+// Stage s of np pencils in place (TIME: decimation in time).
+template <int SGN, bool TIME, class Addr>
+__device__ __forceinline__ void stage(cx<double>* w, const Addr& ad, uint64_t kp, int x, int s, Div np,
+                                      const cx<double>* tw) {
+  const Axis& ax = fresh(kp).ax[x];
+  const int L = ax.L, R0 = ax.r[s], step = ax.step[s];
+  const Div ms = ax.ms[s];
   __syncthreads();
-  axis_pass<RMAX>(w0, scr, d, 3, -1, tw.t3);
-  axis_pass<RMAX>(w0, scr, d, 2, -1, tw.t2);
-  axis_pass<RMAX>(w0, scr, d, 1, -1, tw.t1);
-  for (long long f = threadIdx.x; f < d.n; f += kSmallThreads) {
-    int k1, k2, k3;
-    unravel(f, d, k1, k2, k3);
-    const int c = cls3(k1, k2, k3, d.n1, d.n2, d.n3);
-    const cx<double> h = w0[f];
-    out[f] = c == 0 ? h.re : (c == 1 ? sq2 * h.re : -sq2 * h.im);
+  if (R0 <= kMaxRadix) {
+    with_radix(R0, [&](auto rc) {
+      constexpr int R = decltype(rc)::value;
+      const int total = np.d * (L / R);
+#pragma unroll 1
+      for (int b = threadIdx.x; b < total; b += blockDim.x) {
+        const int bf = np(b), base = ad.base(b - bf * np.d);
+        const int blk = ms(bf), j = bf - blk * ms.d, e0 = blk * ms.d * R + j, a0 = ad.first(base, e0);
+        cx<double> v[R];
+#pragma unroll
+        for (int q = 0; q < R; ++q) v[q] = w[ad.next(a0, base, e0, q, ms.d)];
+        const int js = j * step;
+        if (TIME && ms.d > 1) {
+#pragma unroll
+          for (int q = 1; q < R; ++q) v[q] = cmul(v[q], tw_of(tw, q * js, SGN));
+        }
+        dft_r<R, SGN, double>(v);
+        if (!TIME && ms.d > 1) {
+#pragma unroll
+          for (int q = 1; q < R; ++q) v[q] = cmul(v[q], tw_of(tw, q * js, SGN));
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q) w[ad.next(a0, base, e0, q, ms.d)] = v[q];
+      }
+    });
+  } else {
+    // direct sums, output p of a butterfly by its own thread: a group of
+    // pencils at a time, all its outputs in registers before any is written
+    const int group = max(1, kDirect * (int)blockDim.x / L), unit = L / R0;
+#pragma unroll 1
+    for (int g0 = 0; g0 < np.d; g0 += group) {
+      const int ng = min(group, np.d - g0);
+      cx<double> o[kDirect];
+      int dst[kDirect];
+#pragma unroll
+      for (int k = 0; k < kDirect; ++k) {
+        const int b = threadIdx.x + k * blockDim.x;
+        dst[k] = -1;
+        if (b < ng * L) {
+          const int e = b / ng, base = ad.base(g0 + b - e * ng);
+          const int B = ms.d * R0, blk = e / B, rem = e - blk * B, p = ms(rem), j = rem - p * ms.d;
+          const int inc = TIME ? (p * unit + j * step) % L : p * unit;
+          double re = 0.0, im = 0.0;
+          int idx = 0;
+#pragma unroll 1
+          for (int q = 0; q < R0; ++q) {
+            const cx<double> x = w[ad.at(base, blk * B + j + q * ms.d)], t = tw_of(tw, idx, SGN);
+            re += x.re * t.re - x.im * t.im;
+            im += x.re * t.im + x.im * t.re;
+            idx += inc;
+            if (idx >= L) idx -= L;
+          }
+          o[k] = {re, im};
+          if (!TIME) o[k] = cmul(o[k], tw_of(tw, j * p * step, SGN));
+          dst[k] = ad.at(base, e);
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < kDirect; ++k)
+        if (dst[k] >= 0) w[dst[k]] = o[k];
+      __syncthreads();
+    }
   }
-  __syncthreads();
+}
+
+template <int SGN, bool TIME, class Addr>
+__device__ __forceinline__ void axis_stages(cx<double>* w, const Addr& ad, uint64_t kp, int x, int lo, int hi, Div np,
+                                            const cx<double>* tw) {
+#pragma unroll 1
+  for (int i = lo; i < hi; ++i) stage<SGN, TIME>(w, ad, kp, x, TIME ? hi - 1 - (i - lo) : i, np, tw);
+}
+
+// ------------------------------------------------------------- one problem --
+// the per-problem arrays, each of n doubles, in the problem's workspace
+// (p_beta twice: the H-apply of the new direction reads the old one at k and
+// -k while it writes the new one)
+enum SmallVec {
+  SV_XI, SV_B, SV_Z, SV_N1, SV_N2, SV_HB, SV_S1, SV_S2, SV_XB, SV_XZ, SV_RB, SV_RZ, SV_PB, SV_PB2, SV_PZ, SV_QB,
+  SV_QZ, SV_COUNT
+};
+
+// what the spectrum is formed from and what becomes of it
+enum Mode {
+  M_XI,      // xi = A^T b
+  M_RESID,   // H beta and the residual parts of the iterate
+  M_K,       // q = K p, p.q
+  M_KP       // the same after p <- z + bt p
+};
+
+struct Ctx {
+  uint64_t kp;                // the kernel's arguments: the plan
+  int n;
+  cx<double>* w;              // LDS tile
+  cx<double>* wg;             // the spectrum in the workspace (not resident)
+  const cx<double>* tw;       // LDS: the twiddle tables of axes 1, 2, 3
+  const uint8_t* nat;         // LDS: natural index of a slot, kSmallMaxExtent per axis
+  const uint8_t* obs;
+  const double* sig;
+  double* red;
+  double *v;                  // the arrays
+  double *pb, *pb_old;
+  double lam, bt;
+  __device__ __forceinline__ double* a(int k) const {
+    uint64_t b = (uint64_t)v;   // (as fresh)
+    asm volatile("" : "+s"(b));
+    return (double*)(__attribute__((address_space(1))) double*)b + (long long)k * n;
+  }
+};
+
+// element i of a vector, by a 32-bit offset from its (uniform) base
+__device__ __forceinline__ double& el(double* p, int i) {
+  return *reinterpret_cast<double*>(reinterpret_cast<char*>(p) + ((uint32_t)i << 3));
+}
+__device__ __forceinline__ double el(const double* p, int i) {
+  return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(p) + ((uint32_t)i << 3));
+}
+
+// Loops over a tile's or a vector's values take kBatch of them per thread and
+// round: the loads of all go out before the first is used (one load's
+// latency per round is what such a loop costs on one compute unit).
+constexpr int kBatch = 4;
+
+// A thread's column (k2, m) of the beta side and the external indices of its
+// frequencies k and -k: k1 enters as f0 + k1 s and g0 - k1 s (g0 at k1 = 0 less
+// n1 s), so a loop over k1 costs no division.
+struct Col {
+  int k2, m, f0, g0, s;
+  bool plane;   // m = 0 or N3 / 2: k and -k are two values of the spectrum
+  __device__ __forceinline__ int f(int k1) const { return f0 + k1 * s; }
+  __device__ __forceinline__ int g(int k1, int n1) const { return g0 + (k1 ? n1 - k1 : 0) * s; }
+};
+__device__ __forceinline__ Col column(const Plan& pl, int q) {
+  Col c;
+  c.k2 = pl.dMS(q);
+  c.m = q - c.k2 * pl.MS;
+  c.s = pl.n2 * pl.n3;
+  c.f0 = c.k2 * pl.n3 + c.m;
+  c.g0 = (c.k2 ? pl.n2 - c.k2 : 0) * pl.n3 + (c.m ? pl.n3 - c.m : 0);
+  c.plane = c.m == 0 || 2 * c.m == pl.n3;
+  return c;
+}
+
+// kBatch spectrum values k1 = k, k + dk, .. of a column of the input vector
+// (derivation "map") into LDS (at + k1 as), the direction updated on the way
+// for M_KP.
+__device__ __forceinline__ void map_in(const Ctx& c, const Plan& pl, int mode, const Col& col, int k, int dk, int at,
+                                       int as) {
+  const double rs2 = 0.70710678118654752440;
+  double b[kBatch], bm[kBatch], z[kBatch], zm[kBatch];
+  const double* const x = mode == M_RESID ? c.a(SV_B) : (mode == M_K ? c.pb : c.pb_old);
+#pragma unroll
+  for (int u = 0; u < kBatch; ++u) {
+    const int k1 = min(k + u * dk, pl.n1 - 1);
+    b[u] = el(x, col.f(k1));
+    bm[u] = el(x, col.g(k1, pl.n1));
+  }
+  if (mode == M_KP) {
+    const double* const y = c.a(SV_QB);
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int k1 = min(k + u * dk, pl.n1 - 1);
+      z[u] = el(y, col.f(k1));
+      zm[u] = el(y, col.g(k1, pl.n1));
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      b[u] = z[u] + c.bt * b[u];
+      bm[u] = zm[u] + c.bt * bm[u];
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kBatch; ++u) {
+    const int k1 = k + u * dk;
+    if (k1 >= pl.n1) break;
+    if (mode == M_KP) {
+      el(c.pb, col.f(k1)) = b[u];
+      if (!col.plane) el(c.pb, col.g(k1, pl.n1)) = bm[u];
+    }
+    const int cl = col.plane ? cls3(k1, col.k2, col.m, pl.n1, pl.n2, pl.n3) : 1;
+    c.w[at + k1 * as] = cl == 0 ? cx<double>{b[u], 0.0}
+                                : (cl == 1 ? cx<double>{rs2 * b[u], rs2 * bm[u]} : cx<double>{rs2 * bm[u], -rs2 * b[u]});
+  }
+}
+
+// The output y = H (input) (or xi) at the coordinates of NU values; acc:
+// three maxima, two sums.
+template <int NU>
+__device__ __forceinline__ void out_values(const Ctx& c, int mode, const int* f, const double* h, double* acc) {
+  if (mode == M_XI) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if (f[u] >= 0) {
+        el(c.a(SV_XI), f[u]) = h[u];
+        acc[0] = fmax(acc[0], fabs(h[u]));
+      }
+    return;
+  }
+  double x[5][NU];
+  const double* const p0 = mode == M_RESID ? c.a(SV_B) : c.a(SV_S1);
+  const double* const p1 = mode == M_RESID ? c.a(SV_Z) : c.a(SV_S2);
+  const double* const p2 = mode == M_RESID ? c.a(SV_N1) : c.pb;
+  const double* const p3 = mode == M_RESID ? c.a(SV_N2) : c.a(SV_PZ);
+  const double* const p4 = mode == M_RESID ? c.a(SV_XI) : c.a(SV_QZ);
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int i = max(f[u], 0);
+    x[0][u] = el(p0, i);
+    x[1][u] = el(p1, i);
+    x[2][u] = el(p2, i);
+    x[3][u] = el(p3, i);
+    x[4][u] = mode == M_K ? 0.0 : el(p4, i);
+  }
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    if (f[u] < 0) continue;
+    if (mode == M_RESID) {
+      const double b = x[0][u], z = x[1][u], a1 = x[2][u], a2 = x[3][u];
+      const double fb = h[u] - x[4][u] - a1 + a2, fz = c.lam - a1 - a2;
+      const double c1 = (z + b) * a1, c2 = (z - b) * a2;
+      el(c.a(SV_HB), f[u]) = h[u];
+      acc[0] = fmax(acc[0], fabs(fb));
+      acc[1] = fmax(acc[1], fabs(fz));
+      acc[2] = fmax(acc[2], fmax(c1, c2));
+      acc[3] += c1 + c2;
+      if (!isfinite(fb) || !isfinite(c1) || !isfinite(c2)) acc[4] += 1.0;
+    } else {
+      const double g1 = x[0][u], g2 = x[1][u], pb = x[2][u];
+      double pz = x[3][u];
+      if (mode == M_KP) {
+        pz = x[4][u] + c.bt * pz;
+        el(c.a(SV_PZ), f[u]) = pz;
+      }
+      const double L1 = g1 + g2, L2 = g1 - g2;
+      const double qb = h[u] + L1 * pb + L2 * pz, qz = L2 * pb + L1 * pz;
+      el(c.a(SV_QB), f[u]) = qb;
+      el(c.a(SV_QZ), f[u]) = qz;
+      acc[3] += pb * qb + pz * qz;
+    }
+  }
+}
+// Two spectrum values k1 = k, k + dk of a column: up to four coordinates.
+__device__ __forceinline__ void map_out(const Ctx& c, const Plan& pl, int mode, const Col& col, int k, int dk, int at,
+                                        int as, double* acc) {
+  const double sq2 = 1.41421356237309504880;
+  int f[4];
+  double h[4];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int k1 = k + u * dk, kk = min(k1, pl.n1 - 1);
+    const bool on = k1 < pl.n1;
+    const cx<double> x = c.w[at + kk * as];
+    const int cl = col.plane ? cls3(kk, col.k2, col.m, pl.n1, pl.n2, pl.n3) : 1;
+    f[2 * u] = on ? col.f(kk) : -1;
+    f[2 * u + 1] = on && !col.plane ? col.g(kk, pl.n1) : -1;
+    h[2 * u] = cl == 0 ? x.re : (cl == 1 ? sq2 * x.re : -sq2 * x.im);
+    h[2 * u + 1] = sq2 * x.im;
+  }
+  out_values<4>(c, mode, f, h, acc);
+}
+
+// v: this workgroup's parts (acc of part p passed to put as they are done)
+// combined over the team.
+__device__ __forceinline__ void put_part(const Team& t, int part, const double* acc, int nq) {
+  if (threadIdx.x == 0)
+    for (int q = 0; q < nq; ++q) t.parts[(t.turn * kParts + part) * 5 + q] = acc[q];
+}
+template <int NQ>
+__device__ __forceinline__ void take_parts(Team& t, int parts, double* v, const int* op) {
+  team_sync(t);
+  const double* const p = t.parts + t.turn * kParts * 5;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    double a = p[q];
+    for (int k = 1; k < parts; ++k) a = combine(op[q], a, p[k * 5 + q]);
+    v[q] = a;
+  }
+  t.turn ^= 1;
+}
+
+// The whole apply, in one pass over the resident tile, or in three over
+// tiles of axis-1 columns, planes and columns again; v: the maxima and sums
+// of the output.  (Every kind of stage has one call here, and the solver one
+// call of this: the butterflies of each would be compiled in again.)
+__device__ __forceinline__ void apply(const Ctx& c, Team& team, int mode, double* v) {
+  constexpr int NQ = 5;
+  constexpr int op[NQ] = {1, 1, 1, 0, 0};
+  cx<double>* const w = c.w;
+  const Plan& pl0 = fresh(c.kp);
+  const bool res = pl0.resident, xi = mode == M_XI;
+  for (int ph = xi && !res ? 1 : 0; ph < (res ? 1 : 3); ++ph) {
+    const Plan& plp = fresh(c.kp);
+    const bool cols = !res && ph != 1;             // tiles of axis-1 columns
+    const bool inv1 = !xi && ph == 0, mid = res || ph == 1, out = res || ph == 2;
+    const int nt = res ? 1 : (cols ? (plp.n2 * plp.MS + plp.cols - 1) / plp.cols : (plp.n1 + plp.planes - 1) / plp.planes);
+    const int parts = plp.parts;
+#pragma unroll 1
+    for (int part = res ? 0 : team.rank; part < parts; part += team.G) {
+      double acc[NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
+#pragma unroll 1
+      for (int t = part; t < nt; t += parts) {
+        const Plan& pl = fresh(c.kp);
+        const int C = pl.n2 * pl.MS, T = pl.cols, n3 = pl.n3, last = pl.ax[2].nst - 1;
+        const bool prime = pl.ax[2].r[last] > kMaxRadix;
+        const int q0 = t * T, nc = min(T, C - q0);               // columns
+        const int s0 = res ? 0 : t * pl.planes, np1 = res ? pl.n1 : min(pl.planes, pl.n1 - s0);   // planes
+        const int lt = t == nt - 1 ? 1 : 0, NR = np1 * pl.n2;
+        const Div dH = pl.dH[lt], d2 = pl.dplane[lt];
+        const int H = dH.d;
+        const Rows ad3{pl.MS, pl.M, n3, H};
+        // the thread's columns of the tile on the beta side: column cq + i cw,
+        // k1 = ck, ck + cg, ..
+        const int cw = pl.dcw.d, cg = pl.cgroups, ck = pl.dcw(threadIdx.x), cq = threadIdx.x - ck * cw;
+        // row of the tile and natural index along axis 3 -> sample
+        auto sample = [&](int row, int e) {
+          const int q = pl.dn2(row);
+          return (c.nat[s0 + q] * pl.n2 + c.nat[kSmallMaxExtent + row - q * pl.n2]) * n3 + e;
+        };
+        __syncthreads();
+        if (inv1) {
+#pragma unroll 1
+          for (int q = cq; q < nc; q += cw) {
+            const Col col = column(pl, q0 + q);
+            if (ck >= cg) break;
+            if (col.m < pl.M) {
+#pragma unroll 1
+              for (int k = ck; k < pl.n1; k += kBatch * cg) map_in(c, pl, mode, col, k, cg, q, T);
+            } else {
+#pragma unroll 1
+              for (int k = ck; k < pl.n1; k += cg) w[k * T + q] = {0.0, 0.0};
+            }
+          }
+        } else if (cols) {
+#pragma unroll 1
+          for (int i = threadIdx.x; i < pl.n1 * T; i += blockDim.x) {
+            const int s = pl.dcols(i), q = i - s * T;
+            w[i] = q < nc ? c.wg[s * C + q0 + q] : cx<double>{0.0, 0.0};
+          }
+        } else if (!xi) {
+#pragma unroll 1
+          for (int i = threadIdx.x; i < np1 * C; i += blockDim.x) w[i] = c.wg[s0 * C + i];
+        }
+        // axes 1 and 2 to real space
+#pragma unroll 1
+        for (int x = 0; x < 2; ++x)
+          if (!xi && (x == 0 ? inv1 : mid) && pl.ax[x].L > 1)
+            axis_stages<+1, false>(w, x == 0 ? Lin{pl.dcols, 0, T} : Lin{pl.dMS, C, pl.MS}, c.kp, x, 0, pl.ax[x].nst,
+                                   x == 0 ? pl.dcols : d2, c.tw + (x == 0 ? 0 : pl.n1));
+        if (mid) {
+          const cx<double>* const tw3 = c.tw + pl.n1 + pl.n2;
+          __syncthreads();
+          if (xi) {
+#pragma unroll 1
+            for (int i = threadIdx.x; i < H * n3; i += blockDim.x) {
+              const int g = pl.dn3(i), s = i - g * n3, e = c.nat[2 * kSmallMaxExtent + s];
+              const int fa = sample(g, e), fb = g + H < NR ? sample(g + H, e) : -1;
+              w[ad3.at(ad3.base(g), s)] = {c.obs[fa] ? c.sig[fa] : 0.0, fb >= 0 && c.obs[fb] ? c.sig[fb] : 0.0};
+            }
+          } else {
+#pragma unroll 1
+            for (int i = threadIdx.x; i < H * pl.M; i += blockDim.x) {
+              const int g = pl.dM(i), e = i - g * pl.M;
+              const cx<double> x = w[g * pl.MS + e];
+              const cx<double> y = g + H < NR ? w[(g + H) * pl.MS + e] : cx<double>{0.0, 0.0};
+              if (e == 0 || 2 * e == n3) {   // (real values)
+                w[g * pl.MS + e] = {x.re, y.re};
+              } else {
+                w[g * pl.MS + e] = {x.re - y.im, x.im + y.re};
+                w[(g + H) * pl.MS + e] = {x.re + y.im, y.re - x.im};
+              }
+            }
+            axis_stages<+1, false>(w, ad3, c.kp, 2, 0, prime ? last + 1 : last, dH, tw3);
+            __syncthreads();
+            if (prime) {
+#pragma unroll 1
+              for (int i = threadIdx.x; i < H * n3; i += blockDim.x) {
+                const int s = dH(i), g = i - s * H, e = c.nat[2 * kSmallMaxExtent + s];
+                cx<double>& x = w[ad3.at(ad3.base(g), s)];
+                if (!c.obs[sample(g, e)]) x.re = 0.0;
+                if (g + H >= NR || !c.obs[sample(g + H, e)]) x.im = 0.0;
+              }
+            } else {
+              // the last inverse stage, the mask and the first forward stage
+              // on the same values
+              with_radix(pl.ax[2].r[last], [&](auto rc) {
+                constexpr int R = decltype(rc)::value;
+                const int total = H * (n3 / R);
+#pragma unroll 1
+                for (int b = threadIdx.x; b < total; b += blockDim.x) {
+                  const int bf = dH(b), g = b - bf * H, base = ad3.base(g);
+                  cx<double> u[R];
+#pragma unroll
+                  for (int q = 0; q < R; ++q) u[q] = w[ad3.at(base, bf * R + q)];
+                  dft_r<R, +1, double>(u);
+                  // (a row without a partner: the imaginary part is dropped when unpacked)
+                  const int ra = sample(g, 0), rb = sample(min(g + H, NR - 1), 0);
+#pragma unroll
+                  for (int q = 0; q < R; ++q) {
+                    const int e = c.nat[2 * kSmallMaxExtent + bf * R + q];
+                    const int oa = c.obs[ra + e], ob = c.obs[rb + e];
+                    u[q].re = oa ? u[q].re : 0.0;
+                    u[q].im = ob ? u[q].im : 0.0;
+                  }
+                  dft_r<R, -1, double>(u);
+#pragma unroll
+                  for (int q = 0; q < R; ++q) w[ad3.at(base, bf * R + q)] = u[q];
+                }
+              });
+            }
+          }
+          axis_stages<-1, true>(w, ad3, c.kp, 2, 0, xi || prime ? last + 1 : last, dH, tw3);
+          __syncthreads();
+          const double sc = xi ? 0.5 / sqrt((double)pl.n) : 0.5 / (double)pl.n;
+#pragma unroll 1
+          for (int i = threadIdx.x; i < H * pl.M; i += blockDim.x) {
+            const int g = pl.dM(i), e = i - g * pl.M;
+            const cx<double> y = w[g * pl.MS + e];
+            cx<double> x0, x1;
+            if (e == 0 || 2 * e == n3) {
+              x0 = {2.0 * sc * y.re, 0.0};
+              x1 = {2.0 * sc * y.im, 0.0};
+            } else {
+              const cx<double> z = w[(g + H) * pl.MS + e];
+              x0 = cscale(cx<double>{y.re + z.re, y.im - z.im}, sc);
+              x1 = cscale(cx<double>{y.im + z.im, z.re - y.re}, sc);
+            }
+            w[g * pl.MS + e] = x0;
+            if (g + H < NR) w[(g + H) * pl.MS + e] = x1;
+          }
+        }
+        // axes 2 and 1 back
+#pragma unroll 1
+        for (int x = 1; x >= 0; --x)
+          if ((x == 0 ? out : mid) && pl.ax[x].L > 1)
+            axis_stages<-1, true>(w, x == 0 ? Lin{pl.dcols, 0, T} : Lin{pl.dMS, C, pl.MS}, c.kp, x, 0, pl.ax[x].nst,
+                                  x == 0 ? pl.dcols : d2, c.tw + (x == 0 ? 0 : pl.n1));
+        __syncthreads();
+        if (out) {
+#pragma unroll 1
+          for (int q = cq; q < nc; q += cw) {
+            const Col col = column(pl, q0 + q);
+            if (ck >= cg || col.m >= pl.M) continue;
+#pragma unroll 1
+            for (int k = ck; k < pl.n1; k += 2 * cg) map_out(c, pl, mode, col, k, cg, q, T, acc);
+          }
+        } else if (cols) {
+#pragma unroll 1
+          for (int i = threadIdx.x; i < pl.n1 * T; i += blockDim.x) {
+            const int s = pl.dcols(i), q = i - s * T;
+            if (q < nc) c.wg[s * C + q0 + q] = w[i];
+          }
+        } else {
+#pragma unroll 1
+          for (int i = threadIdx.x; i < np1 * C; i += blockDim.x) c.wg[s0 * C + i] = w[i];
+        }
+      }
+      if (out) {
+        if (mode == M_RESID) block_reduce<NQ>(acc, op, c.red);
+        else if (xi) block_reduce<1>(acc, op, c.red);
+        else block_reduce<1>(acc + 3, op + 3, c.red);
+        if (res) {
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) v[q] = acc[q];
+        } else {
+          put_part(team, part, acc, NQ);
+        }
+      }
+    }
+    if (!res) {
+      if (out) take_parts<NQ>(team, plp.parts, v, op);
+      else team_sync(team);
+    }
+  }
 }
 
 // P^{-1} of one 2x2 block (equation "invprecond1", C = I)
 __device__ __forceinline__ void pinv1(double rb, double rz, double s1, double s2, double& zb, double& zz) {
   const double L1 = s1 + s2, L2 = s1 - s2;
-  const double D = L1 + 4.0 * s1 * s2;
-  zb = (L1 * rb - L2 * rz) / D;
-  zz = (-L2 * rb + (1.0 + L1) * rz) / D;
+  const double inv = 1.0 / (L1 + 4.0 * s1 * s2);
+  zb = (L1 * rb - L2 * rz) * inv;
+  zz = (-L2 * rb + (1.0 + L1) * rz) * inv;
 }
 
 // largest a with v + a dv >= 0 over this thread's share (inf if none)
 __device__ __forceinline__ double ratio(double v, double dv) { return dv < 0.0 ? -v / dv : INFINITY; }
 
-// the per-problem arrays, each of n doubles, in the problem's workspace
-enum SmallVec {
-  SV_XI, SV_B, SV_Z, SV_N1, SV_N2, SV_HB, SV_S1, SV_S2, SV_XB, SV_XZ, SV_RB, SV_RZ, SV_PB, SV_PZ, SV_QB, SV_QZ,
-  SV_COUNT
-};
-
-template <int RMAX>
-__global__ void __launch_bounds__(kSmallThreads)
-k_small_solve(int n1, int n2, int n3, const double* __restrict__ signals, const uint8_t* __restrict__ observed,
+__global__ void __launch_bounds__(kMaxThreads)
+k_small_solve(Plan pl, const double* __restrict__ signals, const uint8_t* __restrict__ observed,
               const double* __restrict__ lambdas, double lambda_frac, double* __restrict__ beta_out,
               double* __restrict__ info, char* __restrict__ ws, long long ws_stride, const cx<double>* __restrict__ tw,
-              SmallOpts o, int lds_spectrum) {
+              unsigned* __restrict__ counters, int count, int G, SmallOpts o) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ double red[kSmallWaves];
-  const SmallDims d{n1, n2, n3, (long long)n1 * n2 * n3};
-  const long long n = d.n;
-  const int p = blockIdx.x;
-  const double* sig = signals + (long long)p * n;
-  const uint8_t* obs = observed + (long long)p * n;
-  double* v = reinterpret_cast<double*>(ws + (long long)p * ws_stride);
-  // the spectrum and, for a length without the register pass, its scratch
-  cx<double>* w0 = lds_spectrum ? reinterpret_cast<cx<double>*>(smem)
-                                : reinterpret_cast<cx<double>*>(v + (long long)SV_COUNT * n);
-  cx<double>* w1 = w0 + n;
-  const SmallTw T{tw, tw + n1, tw + n1 + n2};
-  double *xi = v + SV_XI * n, *be = v + SV_B * n, *zv = v + SV_Z * n, *nu1 = v + SV_N1 * n,
-         *nu2 = v + SV_N2 * n, *hb = v + SV_HB * n, *g1 = v + SV_S1 * n, *g2 = v + SV_S2 * n, *xb = v + SV_XB * n,
-         *xz = v + SV_XZ * n, *rb = v + SV_RB * n, *rz = v + SV_RZ * n, *pb = v + SV_PB * n, *pz = v + SV_PZ * n,
-         *qb = v + SV_QB * n, *qz = v + SV_QZ * n;
-
-  // xi = A^T b_hat, lambda, the starting point beta = 0, z = |xi|_inf (1 if 0),
-  // nu = lambda / 2 (reading "barrier strategy")
-  at_apply<RMAX>(sig, obs, xi, d, T, w0, w1);
-  double xinf = 0.0;
-  for (long long f = threadIdx.x; f < n; f += kSmallThreads) xinf = fmax(xinf, fabs(xi[f]));
-  xinf = block_reduce(xinf, 1, red);
-  const double lam = lambdas ? lambdas[p] : lambda_frac * xinf;
-  const double z0 = xinf > 0.0 ? xinf : 1.0;
-  for (long long f = threadIdx.x; f < n; f += kSmallThreads) {
-    be[f] = 0.0;
-    zv[f] = z0;
-    nu1[f] = 0.5 * lam;
-    nu2[f] = 0.5 * lam;
-  }
+  __shared__ double red[5 * kMaxWaves];
+  __shared__ uint8_t nat[3 * kSmallMaxExtent];
+  __shared__ int bad;
+  // workgroups go to the 8 XCDs in turn: a team stays on one (its vectors and
+  // spectrum in that L2)
+  const int n = pl.n, prob = G == 1 ? (int)blockIdx.x : (int)blockIdx.x / (8 * G) * 8 + (int)blockIdx.x % 8;
+  if (prob >= count) return;
+  if (threadIdx.x == 0) bad = 0;
+  double* const v = reinterpret_cast<double*>(ws + (long long)prob * ws_stride);
+  cx<double>* const twl = reinterpret_cast<cx<double>*>(smem);
+#pragma unroll 1
+  for (int i = threadIdx.x; i < pl.n1 + pl.n2 + pl.n3; i += blockDim.x) twl[i] = tw[i];
+  // slot -> natural index of each axis
+#pragma unroll 1
+  for (int x = 0; x < 3; ++x)
+#pragma unroll 1
+    for (int k = threadIdx.x; k < pl.ax[x].L; k += blockDim.x) {
+      int slot = 0, r = k;
+      for (int s = 0; s < pl.ax[x].nst; ++s) {
+        slot = slot * pl.ax[x].r[s] + r % pl.ax[x].r[s];
+        r /= pl.ax[x].r[s];
+      }
+      nat[x * kSmallMaxExtent + slot] = (uint8_t)k;
+    }
   __syncthreads();
-
-  int it = 0, cg_total = 0, status = 1;   // 1: not converged (iteration limit)
-  double rel = INFINITY, mu = 0.0;
-  for (;; ++it) {
-    // residual of the iterate (equation "kkt") and its relative size
-    h_apply<RMAX>(be, hb, obs, d, T, w0, w1);
-    double fb = 0.0, fz = 0.0, cmax = 0.0, csum = 0.0;
-    bool bad = false;
-    for (long long f = threadIdx.x; f < n; f += kSmallThreads) {
-      const double s1 = zv[f] + be[f], s2 = zv[f] - be[f];
-      const double a = hb[f] - xi[f] - nu1[f] + nu2[f];
-      const double b = lam - nu1[f] - nu2[f];
-      const double c1 = s1 * nu1[f], c2 = s2 * nu2[f];
-      fb = fmax(fb, fabs(a));
-      fz = fmax(fz, fabs(b));
-      cmax = fmax(cmax, fmax(c1, c2));
-      csum += c1 + c2;
-      bad = bad || !isfinite(a) || !isfinite(c1) || !isfinite(c2);
-    }
-    fb = block_reduce(fb, 1, red);
-    fz = block_reduce(fz, 1, red);
-    cmax = block_reduce(cmax, 1, red);
-    csum = block_reduce(csum, 0, red);
-    const double nbad = block_reduce(bad ? 1.0 : 0.0, 0, red);
-    mu = csum / (2.0 * (double)n);
-    rel = fmax(fmax(fb, fz), cmax) / (1.0 + xinf);
-    if (nbad > 0.0) {
-      status = -2;   // non-finite iterate
-      break;
-    }
-    if (rel <= o.tol) {
-      status = 0;
-      break;
-    }
-    if (it >= o.max_iter) break;
-
-    // Newton system (equation "condensedkkt"): Sigma_j = nu_j / s_j and the
-    // right-hand side from equation "kktmu" (reading "Newton RHS"), in r;
-    // PCG from x = 0 on K with the paper's P
-    const double smu = o.sigma * mu;
-    const double eta = fmin(o.cg_rtol, 0.1 * rel);
-    double rho = 0.0;
-    for (long long f = threadIdx.x; f < n; f += kSmallThreads) {
-      const double s1 = zv[f] + be[f], s2 = zv[f] - be[f];
-      const double i1 = 1.0 / s1, i2 = 1.0 / s2;
-      const double a1 = nu1[f] * i1, a2 = nu2[f] * i2;
-      g1[f] = a1;
-      g2[f] = a2;
-      const double r1 = -(hb[f] - xi[f]) + smu * (i1 - i2);
-      const double r2 = -lam + smu * (i1 + i2);
-      rb[f] = r1;
-      rz[f] = r2;
-      xb[f] = 0.0;
-      xz[f] = 0.0;
-      double w1v, w2v;
-      pinv1(r1, r2, a1, a2, w1v, w2v);
-      pb[f] = w1v;
-      pz[f] = w2v;
-      rho += r1 * w1v + r2 * w2v;
-    }
-    rho = block_reduce(rho, 0, red);
-    const double tol = fmax(o.cg_atol, eta * sqrt(fmax(rho, 0.0)));
-    int cg = 0;
-    while (sqrt(fmax(rho, 0.0)) > tol && cg < o.cg_max) {
-      // q = K p (H p_beta plus the Sigma terms)
-      h_apply<RMAX>(pb, qb, obs, d, T, w0, w1);
-      double pq = 0.0;
-      for (long long f = threadIdx.x; f < n; f += kSmallThreads) {
-        const double L1 = g1[f] + g2[f], L2 = g1[f] - g2[f];
-        const double a = qb[f] + L1 * pb[f] + L2 * pz[f];
-        const double b = L2 * pb[f] + L1 * pz[f];
-        qb[f] = a;
-        qz[f] = b;
-        pq += pb[f] * a + pz[f] * b;
+  Ctx c;
+  c.kp = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();   // (the plan is the first argument)
+  c.n = n;
+  c.w = twl + (pl.n1 + pl.n2 + pl.n3);
+  c.wg = reinterpret_cast<cx<double>*>(v + ((long long)SV_COUNT * n + 1) / 2 * 2);
+  c.tw = twl;
+  c.nat = nat;
+  c.obs = observed + (long long)prob * n;
+  c.sig = signals + (long long)prob * n;
+  c.red = red;
+  c.v = v;
+  c.pb = c.a(SV_PB);
+  c.pb_old = c.a(SV_PB2);
+  const int parts = pl.parts;
+  Team team{G, G == 1 ? 0 : (int)blockIdx.x / 8 % G, 0u, counters + 16 * (G == 1 ? 0 : prob),
+            reinterpret_cast<double*>(c.wg + (pl.resident ? 0 : pl.n1 * pl.n2 * pl.MS)), 0, &bad};
+  // sum (or minimum) over the coordinates, in fixed parts: f(load(i)) with the
+  // loads of two coordinates ahead of the first use
+  auto over = [&](int op, auto load, auto f) {
+    double tot = 0.0;
+#pragma unroll 1
+    for (int part = team.rank; part < parts; part += team.G) {
+      const int lo = (int)((long long)n * part / parts), hi = (int)((long long)n * (part + 1) / parts);
+      double a = op == 2 ? INFINITY : 0.0;
+#pragma unroll 1
+      for (int i = lo + (int)threadIdx.x; i < hi; i += 2 * blockDim.x) {
+        const int j = i + blockDim.x;
+        const auto x = load(i), y = load(min(j, n - 1));
+        a = combine(op, a, f(i, x));
+        if (j < hi) a = combine(op, a, f(j, y));
       }
-      pq = block_reduce(pq, 0, red);
-      const double alpha = rho / pq;
-      double rn = 0.0;
-      for (long long f = threadIdx.x; f < n; f += kSmallThreads) {
-        xb[f] += alpha * pb[f];
-        xz[f] += alpha * pz[f];
-        const double r1 = rb[f] - alpha * qb[f], r2 = rz[f] - alpha * qz[f];
-        rb[f] = r1;
-        rz[f] = r2;
+      block_reduce<1>(&a, &op, red);
+      tot = a;
+      if (parts > 1) put_part(team, part, &a, 1);
+    }
+    if (parts > 1) take_parts<1>(team, parts, &tot, &op);
+    return tot;
+  };
+
+  // One apply after another; what follows each decides on the next:
+  //   xi = A^T b_hat: lambda, the starting point beta = 0, z = |xi|_inf (1 if
+  //     0), nu = lambda / 2 (reading "barrier strategy"), then the residual;
+  //   H beta: the KKT residual, then the Newton system and its first q = K p;
+  //   q = K p: a PCG step, then the next direction's, or the step of the
+  //     iterate and the next residual.
+  int it = 0, cg = 0, cg_total = 0, status = 1;   // 1: not converged (iteration limit)
+  double rel = INFINITY, mu = 0.0, xinf = 0.0, smu = 0.0, rho = 0.0, tol = 0.0;
+  c.lam = 0.0;
+  c.bt = 0.0;
+  for (int mode = M_XI;;) {
+    double q[5];
+    apply(c, team, mode, q);
+    if (bad) {   // (written before a barrier that all have passed)
+      status = -3;
+      break;
+    }
+    if (mode == M_XI) {
+      xinf = q[0];
+      c.lam = lambdas ? lambdas[prob] : lambda_frac * xinf;
+      const double z0 = xinf > 0.0 ? xinf : 1.0;
+      double *const be = c.a(SV_B), *const zv = c.a(SV_Z), *const nu1 = c.a(SV_N1), *const nu2 = c.a(SV_N2);
+      for (int f = team.rank * blockDim.x + threadIdx.x; f < n; f += team.G * blockDim.x) {
+        el(be, f) = 0.0;
+        el(zv, f) = z0;
+        el(nu1, f) = 0.5 * c.lam;
+        el(nu2, f) = 0.5 * c.lam;
+      }
+      team_sync(team);
+      mode = M_RESID;
+      continue;
+    }
+    if (mode == M_RESID) {
+      // the iterate's relative residual (equation "kkt")
+      mu = q[3] / (2.0 * (double)n);
+      rel = fmax(fmax(q[0], q[1]), q[2]) / (1.0 + xinf);
+      if (q[4] > 0.0) {
+        status = -2;   // non-finite iterate
+        break;
+      }
+      if (rel <= o.tol) {
+        status = 0;
+        break;
+      }
+      if (it >= o.max_iter) break;
+      // Newton system (equation "condensedkkt"): Sigma_j = nu_j / s_j and the
+      // right-hand side from equation "kktmu" (reading "Newton RHS"), in r;
+      // PCG from x = 0 on K with the paper's P
+      smu = o.sigma * mu;
+      const double eta = fmin(o.cg_rtol, 0.1 * rel), lam = c.lam;
+      const double *const be = c.a(SV_B), *const zv = c.a(SV_Z), *const nu1 = c.a(SV_N1), *const nu2 = c.a(SV_N2),
+                   *const hb = c.a(SV_HB), *const xi = c.a(SV_XI);
+      double *const g1 = c.a(SV_S1), *const g2 = c.a(SV_S2), *const rb = c.a(SV_RB), *const rz = c.a(SV_RZ),
+             *const pz = c.a(SV_PZ);
+      struct State { double b, z, a1, a2, h, x; };
+      rho = over(0, [&](int f) { return State{el(be, f), el(zv, f), el(nu1, f), el(nu2, f), el(hb, f), el(xi, f)}; }, [&](int f, State s) {
+        const double s1 = s.z + s.b, s2 = s.z - s.b;
+        const double i1 = 1.0 / s1, i2 = 1.0 / s2;
+        const double a1 = s.a1 * i1, a2 = s.a2 * i2;
+        el(g1, f) = a1;
+        el(g2, f) = a2;
+        const double r1 = -(s.h - s.x) + smu * (i1 - i2);
+        const double r2 = -lam + smu * (i1 + i2);
+        el(rb, f) = r1;
+        el(rz, f) = r2;
         double w1v, w2v;
-        pinv1(r1, r2, g1[f], g2[f], w1v, w2v);
-        qb[f] = w1v;   // z = P^{-1} r, kept in q until the direction update
-        qz[f] = w2v;
-        rn += r1 * w1v + r2 * w2v;
-      }
-      rn = block_reduce(rn, 0, red);
-      const double bt = rn / rho;
+        pinv1(r1, r2, a1, a2, w1v, w2v);
+        el(c.pb, f) = w1v;
+        el(pz, f) = w2v;
+        return r1 * w1v + r2 * w2v;
+      });
+      tol = fmax(o.cg_atol, eta * sqrt(fmax(rho, 0.0)));
+      cg = 0;
+    } else {
+      const double alpha = rho / q[3];
+      const bool first = cg == 0;
+      const double *const pz = c.a(SV_PZ), *const g1 = c.a(SV_S1), *const g2 = c.a(SV_S2);
+      double *const xb = c.a(SV_XB), *const xz = c.a(SV_XZ), *const rb = c.a(SV_RB), *const rz = c.a(SV_RZ),
+             *const qb = c.a(SV_QB), *const qz = c.a(SV_QZ);
+      struct Krylov { double pb, pz, xb, xz, rb, rz, qb, qz, g1, g2; };
+      auto load = [&](int f) {
+        return Krylov{el(c.pb, f), el(pz, f), first ? 0.0 : el(xb, f), first ? 0.0 : el(xz, f), el(rb, f), el(rz, f), el(qb, f), el(qz, f), el(g1, f),
+                      el(g2, f)};
+      };
+      const double rn = over(0, load, [&](int f, Krylov k) {
+        el(xb, f) = k.xb + alpha * k.pb;
+        el(xz, f) = k.xz + alpha * k.pz;
+        const double r1 = k.rb - alpha * k.qb, r2 = k.rz - alpha * k.qz;
+        el(rb, f) = r1;
+        el(rz, f) = r2;
+        double w1v, w2v;
+        pinv1(r1, r2, k.g1, k.g2, w1v, w2v);
+        el(qb, f) = w1v;   // z = P^{-1} r, kept in q until the direction update
+        el(qz, f) = w2v;
+        return r1 * w1v + r2 * w2v;
+      });
+      c.bt = rn / rho;
       rho = rn;
-      for (long long f = threadIdx.x; f < n; f += kSmallThreads) {
-        pb[f] = qb[f] + bt * pb[f];
-        pz[f] = qz[f] + bt * pz[f];
-      }
-      __syncthreads();
       ++cg;
     }
+    if (sqrt(fmax(rho, 0.0)) > tol && cg < o.cg_max) {
+      mode = cg == 0 ? M_K : M_KP;
+      if (cg > 0) {
+        double* const t = c.pb;
+        c.pb = c.pb_old;
+        c.pb_old = t;
+      }
+      continue;
+    }
     cg_total += cg;
-
     // multiplier direction, step to the boundary and update
-    double amax = INFINITY;
-    for (long long f = threadIdx.x; f < n; f += kSmallThreads) {
-      const double s1 = zv[f] + be[f], s2 = zv[f] - be[f];
-      const double ds1 = xb[f] + xz[f], ds2 = xz[f] - xb[f];
-      const double dn1 = smu / s1 - nu1[f] - g1[f] * ds1;
-      const double dn2 = smu / s2 - nu2[f] - g2[f] * ds2;
-      rb[f] = dn1;
-      rz[f] = dn2;
-      amax = fmin(amax, fmin(fmin(ratio(s1, ds1), ratio(s2, ds2)), fmin(ratio(nu1[f], dn1), ratio(nu2[f], dn2))));
-    }
-    amax = block_reduce(amax, 2, red);
+    const bool none = cg == 0;
+    double *const be = c.a(SV_B), *const zv = c.a(SV_Z), *const nu1 = c.a(SV_N1), *const nu2 = c.a(SV_N2),
+           *const xb = c.a(SV_XB), *const xz = c.a(SV_XZ), *const rb = c.a(SV_RB), *const rz = c.a(SV_RZ);
+    const double *const g1 = c.a(SV_S1), *const g2 = c.a(SV_S2);
+    struct Dir { double b, z, a1, a2, d1, d2, g1, g2; };
+    auto load = [&](int f) {
+      return Dir{el(be, f), el(zv, f), el(nu1, f), el(nu2, f), none ? 0.0 : el(xb, f), none ? 0.0 : el(xz, f), el(g1, f), el(g2, f)};
+    };
+    const double amax = over(2, load, [&](int f, Dir d) {
+      if (none) {
+        el(xb, f) = 0.0;
+        el(xz, f) = 0.0;
+      }
+      const double s1 = d.z + d.b, s2 = d.z - d.b;
+      const double ds1 = d.d1 + d.d2, ds2 = d.d2 - d.d1;
+      const double dn1 = smu / s1 - d.a1 - d.g1 * ds1;
+      const double dn2 = smu / s2 - d.a2 - d.g2 * ds2;
+      el(rb, f) = dn1;
+      el(rz, f) = dn2;
+      return fmin(fmin(ratio(s1, ds1), ratio(s2, ds2)), fmin(ratio(d.a1, dn1), ratio(d.a2, dn2)));
+    });
     const double step = fmin(1.0, o.tau * amax);
-    for (long long f = threadIdx.x; f < n; f += kSmallThreads) {
-      be[f] += step * xb[f];
-      zv[f] += step * xz[f];
-      nu1[f] += step * rb[f];
-      nu2[f] += step * rz[f];
+#pragma unroll 1
+    for (int part = team.rank; part < parts; part += team.G) {
+      const int lo = (int)((long long)n * part / parts), hi = (int)((long long)n * (part + 1) / parts);
+#pragma unroll 1
+      for (int i = lo + (int)threadIdx.x; i < hi; i += 2 * blockDim.x) {
+        struct Step { double b, z, a1, a2, xb, xz, r1, r2; };
+        auto get = [&](int f) { return Step{el(be, f), el(zv, f), el(nu1, f), el(nu2, f), el(xb, f), el(xz, f), el(rb, f), el(rz, f)}; };
+        auto put = [&](int f, const Step& d) {
+          el(be, f) = d.b + step * d.xb;
+          el(zv, f) = d.z + step * d.xz;
+          el(nu1, f) = d.a1 + step * d.r1;
+          el(nu2, f) = d.a2 + step * d.r2;
+        };
+        const int j = i + blockDim.x;
+        const Step x = get(i), y = get(min(j, n - 1));
+        put(i, x);
+        if (j < hi) put(j, y);
+      }
     }
-    __syncthreads();
+    team_sync(team);
+    mode = M_RESID;
+    ++it;
   }
-  for (long long f = threadIdx.x; f < n; f += kSmallThreads) beta_out[(long long)p * n + f] = be[f];
-  if (threadIdx.x == 0) {
-    double* out = info + (long long)p * CSIPM_SMALL_INFO;
+  __syncthreads();
+  for (int f = team.rank * blockDim.x + threadIdx.x; f < n; f += team.G * blockDim.x)
+    beta_out[(long long)prob * n + f] = el(c.a(SV_B), f);
+  if (threadIdx.x == 0 && team.rank == 0) {
+    double* out = info + (long long)prob * CSIPM_SMALL_INFO;
     out[0] = (double)status;
     out[1] = (double)it;
     out[2] = (double)cg_total;
     out[3] = rel;
     out[4] = mu;
-    out[5] = lam;
+    out[5] = c.lam;
   }
+}
+
+// Radices of an axis: primes above 8 first, then the fewest of 2 .. 8 (the
+// smallest sum among those, largest first).
+void search(int L, int top, int depth, int* cur, int sum, int* best, int& nbest, int& sbest) {
+  if (L == 1) {
+    if (nbest == 0 || depth < nbest || (depth == nbest && sum < sbest)) {
+      nbest = depth;
+      sbest = sum;
+      std::copy(cur, cur + depth, best);
+    }
+    return;
+  }
+  if (depth == kStages || (nbest && depth >= nbest)) return;
+  for (int r = std::min(top, kMaxRadix); r >= 2; --r)
+    if (L % r == 0) {
+      cur[depth] = r;
+      search(L / r, r, depth + 1, cur, sum + r, best, nbest, sbest);
+    }
+}
+
+Axis make_axis(int L) {
+  Axis ax{};
+  ax.L = L;
+  int rest = L, n = 0;
+  for (int p = 11; p <= L; ++p)
+    while (rest % p == 0 && [&] { for (int d = 2; d * d <= p; ++d) if (p % d == 0) return false; return true; }()) {
+      ax.r[n++] = p;
+      rest /= p;
+    }
+  if (rest > 1) {
+    int cur[kStages], best[kStages], nb = 0, sb = 0;
+    search(rest, kMaxRadix, 0, cur, 0, best, nb, sb);
+    for (int i = 0; i < nb; ++i) ax.r[n++] = best[i];
+  }
+  if (n == 0) ax.r[n++] = 1;
+  ax.nst = n;
+  int B = L;
+  for (int s = 0; s < n; ++s) {
+    ax.step[s] = L / B;
+    ax.ms[s] = make_div(B / ax.r[s]);
+    B /= ax.r[s];
+  }
+  return ax;
+}
+
+Plan make_plan(int n1, int n2, int n3) {
+  Plan pl{};
+  pl.n1 = n1;
+  pl.n2 = n2;
+  pl.n3 = n3;
+  pl.n = n1 * n2 * n3;
+  pl.M = n3 / 2 + 1;
+  pl.MS = pl.M | 1;
+  const int L[3] = {n1, n2, n3};
+#pragma unroll 1
+  for (int x = 0; x < 3; ++x) pl.ax[x] = make_axis(L[x]);
+  const int C = n2 * pl.MS, rows = (n1 * n2 + 1) / 2 * 2;
+  pl.resident = rows * pl.MS <= kResident;
+  if (pl.resident) {
+    pl.tile = rows * pl.MS;
+    pl.cols = C;
+    pl.parts = 1;
+  } else {
+    // about as many tiles of columns and of planes as parts
+    auto up8 = [](int x) { return (x + 7) / 8 * 8; };
+    pl.parts = pl.n < kLarge ? kParts / 2 : kParts;
+    pl.cols = std::min({up8((C + pl.parts - 1) / pl.parts), kMaxThreads, kTile / n1 / 8 * 8});
+    pl.planes = std::min((n1 + pl.parts - 1) / pl.parts, std::max(1, kTile / ((n2 + 1) / 2 * 2 * pl.MS)));
+    pl.tile = std::max(pl.cols * n1, ((pl.planes * n2 + 1) / 2 * 2) * pl.MS);
+  }
+  pl.threads = kMaxThreads;
+  pl.dM = make_div(pl.M);
+  pl.dMS = make_div(pl.MS);
+  pl.dn2 = make_div(n2);
+  pl.dn3 = make_div(n3);
+  pl.dcols = make_div(pl.cols);
+  const int full = pl.resident ? n1 : pl.planes, rest = n1 % full ? n1 % full : full;
+  for (int k = 0; k < 2; ++k) {
+    const int np = k ? rest : full;
+    pl.dH[k] = make_div((np * n2 + 1) / 2);
+    pl.dplane[k] = make_div(np * pl.MS);
+  }
+  pl.dcw = make_div(std::min(pl.cols, pl.threads));
+  pl.cgroups = std::max(1, pl.threads / pl.cols);
+  return pl;
 }
 
 }  // namespace
@@ -436,47 +1047,58 @@ bool small_supported(int n1, int n2, int n3) {
          n3 <= kSmallMaxExtent;
 }
 
-namespace {
-// complex buffers of the transforms: the spectrum, and a scratch copy when
-// an extent has no register pass
-int spectrum_buffers(int n1, int n2, int n3) {
-  const auto reg = [](int L) { return L == 1 || reg_length(L); };
-  return reg(n1) && reg(n2) && reg(n3) ? 1 : 2;
+size_t small_front_bytes(int n1, int n2, int n3) {
+  const size_t b = sizeof(cx<double>) * (size_t)(n1 + n2 + n3) + 64 * (size_t)kSmallTeams;
+  return (b + 255) & ~(size_t)255;
 }
-bool spectrum_in_lds(int n1, int n2, int n3) {
-  const long long n = (long long)n1 * n2 * n3;
-  return (long long)spectrum_buffers(n1, n2, n3) * n * (long long)sizeof(cx<double>) <= kSmallLdsBytes;
-}
-}  // namespace
 
 size_t small_problem_bytes(int n1, int n2, int n3) {
-  const long long n = (long long)n1 * n2 * n3;
-  const bool lds = spectrum_in_lds(n1, n2, n3);
-  // SV_COUNT real arrays, and the spectrum buffers when they do not sit in LDS
-  size_t b = sizeof(double) * (size_t)n * (size_t)SV_COUNT +
-             (lds ? 0 : (size_t)spectrum_buffers(n1, n2, n3) * sizeof(cx<double>) * (size_t)n);
+  if (tiny_grid(n1, n2, n3)) return tiny_problem_bytes(n1, n2, n3);
+  const Plan pl = make_plan(n1, n2, n3);
+  // SV_COUNT real arrays, and, when the spectrum does not sit in LDS, it and
+  // the parts of the sums
+  size_t b = sizeof(double) * (((size_t)pl.n * (size_t)SV_COUNT + 1) / 2 * 2) +
+             (pl.resident ? 0 : (size_t)n1 * n2 * pl.MS * sizeof(cx<double>) + 2 * kParts * 5 * sizeof(double));
   return (b + 255) & ~(size_t)255;
 }
 
 hipError_t small_launch(int n1, int n2, int n3, int count, const double* signals, const uint8_t* observed,
                         const double* lambdas, double lambda_frac, double* beta_out, double* info, char* ws,
-                        const cx<double>* tw, const SmallOpts& o, hipStream_t s) {
-  const long long n = (long long)n1 * n2 * n3;
-  const bool lds = spectrum_in_lds(n1, n2, n3);
-  const size_t shm = lds ? (size_t)spectrum_buffers(n1, n2, n3) * sizeof(cx<double>) * (size_t)n : 0;
-  const bool has32 = n1 == 32 || n2 == 32 || n3 == 32;
-  const void* kern = has32 ? (const void*)k_small_solve<32> : (const void*)k_small_solve<16>;
+                        const cx<double>* tw, unsigned* counters, const SmallOpts& o, hipStream_t s) {
+  if (tiny_grid(n1, n2, n3))
+    return tiny_launch(n1, n2, n3, count, signals, observed, lambdas, lambda_frac, beta_out, info, ws, tw, o, s);
+  const Plan pl = make_plan(n1, n2, n3);
+  const size_t shm = (size_t)(pl.tile + n1 + n2 + n3) * sizeof(cx<double>);
   if (shm > 65536) {
-    const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+    const hipError_t e =
+        hipFuncSetAttribute((const void*)k_small_solve, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
     if (e != hipSuccess) return e;
   }
-  const long long stride = (long long)small_problem_bytes(n1, n2, n3);
-  if (has32)
-    hipLaunchKernelGGL(k_small_solve<32>, dim3(count), dim3(kSmallThreads), shm, s, n1, n2, n3, signals, observed,
-                       lambdas, lambda_frac, beta_out, info, ws, stride, tw, o, lds ? 1 : 0);
-  else
-    hipLaunchKernelGGL(k_small_solve<16>, dim3(count), dim3(kSmallThreads), shm, s, n1, n2, n3, signals, observed,
-                       lambdas, lambda_frac, beta_out, info, ws, stride, tw, o, lds ? 1 : 0);
+  long long stride = (long long)small_problem_bytes(n1, n2, n3);
+  int G = 1, one = 1;
+  if (!pl.resident && count <= kSmallTeams) {
+    // teams of as many workgroups as are resident together, launched
+    // cooperatively (which guarantees it, whatever else the device runs)
+    int dev = 0, cus = 0, per = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, (const void*)k_small_solve, pl.threads, shm) == hipSuccess) {
+      const int slots = (count + 7) / 8 * 8;
+      while (2 * G <= pl.parts && 2 * G * slots <= cus * per) G *= 2;
+    }
+    if (G > 1) {
+      Plan plan = pl;
+      SmallOpts opts = o;
+      void* args[] = {&plan, &signals, &observed, &lambdas, &lambda_frac, &beta_out, &info, &ws, &stride, &tw,
+                      &counters, &count, &G, &opts};
+      const hipError_t e = hipLaunchCooperativeKernel((const void*)k_small_solve, dim3((count + 7) / 8 * 8 * G),
+                                                      dim3(pl.threads), args, (unsigned)shm, s);
+      if (e == hipSuccess) return e;
+      (void)hipGetLastError();   // (refused: one workgroup per problem)
+    }
+  }
+  hipLaunchKernelGGL(k_small_solve, dim3(count), dim3(pl.threads), shm, s, pl, signals, observed, lambdas, lambda_frac,
+                     beta_out, info, ws, stride, tw, counters, count, one, o);
   return hipGetLastError();
 }
 
@@ -486,8 +1108,7 @@ using csipm::cx;
 
 extern "C" size_t csipm_small_workspace_bytes(int n1, int n2, int n3, int count) {
   if (!csipm::small_supported(n1, n2, n3) || count < 1) return 0;
-  const size_t tw = (sizeof(cx<double>) * (size_t)(n1 + n2 + n3) + 255) & ~(size_t)255;
-  return tw + (size_t)count * csipm::small_problem_bytes(n1, n2, n3);
+  return csipm::small_front_bytes(n1, n2, n3) + (size_t)count * csipm::small_problem_bytes(n1, n2, n3);
 }
 
 extern "C" csipm_status csipm_solve_small_batch(int n1, int n2, int n3, int count, const double* d_signals,
@@ -527,16 +1148,19 @@ extern "C" csipm_status csipm_solve_small_batch(int n1, int n2, int n3, int coun
       const long double a = -2.0L * 3.141592653589793238462643383279502884L * (long double)q / (long double)L;
       h.push_back({(double)cosl(a), (double)sinl(a)});
     }
+  // and, behind them, the team counters, 0 (64 bytes each)
+  const size_t ntw = h.size();
+  h.resize(ntw + 4 * (size_t)csipm::kSmallTeams, cx<double>{0.0, 0.0});
   char* ws = reinterpret_cast<char*>(d_workspace);
   hipError_t e = hipMemcpyAsync(ws, h.data(), h.size() * sizeof(cx<double>), hipMemcpyHostToDevice, s);
   // (the host vector must outlive the copy)
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  const size_t tw = (sizeof(cx<double>) * h.size() + 255) & ~(size_t)255;
   const csipm::SmallOpts o{opts->tol, opts->max_iter, opts->cg_max, opts->cg_rtol, opts->cg_atol, opts->sigma,
                            opts->tau};
   if (e == hipSuccess)
     e = csipm::small_launch(n1, n2, n3, count, d_signals, d_observed, d_lambdas, lambda_frac, d_beta_out, d_info,
-                            ws + tw, reinterpret_cast<const cx<double>*>(ws), o, s);
+                            ws + csipm::small_front_bytes(n1, n2, n3), reinterpret_cast<const cx<double>*>(ws),
+                            reinterpret_cast<unsigned*>(ws + ntw * sizeof(cx<double>)), o, s);
   if (e != hipSuccess) {
     csipm::noctx_set_error(std::string("solve_small_batch: ") + hipGetErrorString(e));
     return CSIPM_EHIP;

@@ -1,0 +1,54 @@
+"""csipm_solve_small_batch where its transforms can go wrong: prime extents
+(stages of direct sums, on each axis, alone and beside other radices),
+extents 1 and 2, an odd count of rows, the largest spectra that stay in LDS
+and the smallest that do not, extent 64, several tiles with a ragged last one,
+against the oracle's interior-point solve; and a grid outside LDS in a batch
+against alone, bit for bit."""
+import numpy as np
+import pytest
+
+from oracle import ipm
+from paper_2502_04217_amd import workload as wl
+from tests._gpu_common import need_gpu, rel2, say
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-10
+
+
+def _workload(shape, seed):
+    rng = np.random.default_rng(seed)
+    if min(shape[0] * shape[1], shape[2]) >= 3:
+        return wl.make_workload(shape, n_freq=8, amplitude="normal", snr_db=20.0, half_width=-1, period=1,
+                                dropout=0.15, seed=seed)
+    obs = (rng.random(shape) > 0.15).astype(np.uint8)
+    obs.ravel()[0] = 1
+    sig = rng.standard_normal(shape) * obs
+    return wl.Workload(shape, sig, obs, sig, np.zeros((0, 3), np.int64), np.zeros(0, np.complex128), 0.0)
+
+
+@pytest.mark.parametrize("shape", [(11, 4, 6), (4, 13, 5), (5, 3, 11), (3, 22, 26), (1, 1, 37), (7, 1, 1), (5, 2, 2),
+                                   (1, 6, 1), (3, 5, 4), (8, 8, 8), (1, 1, 1), (16, 8, 8), (3, 7, 20), (64, 2, 9), (2, 64, 3), (3, 3, 64), (27, 27, 24),
+                                   (24, 24, 31), (20, 30, 32), (59, 12, 30)], ids=lambda s: "x".join(map(str, s)))
+def test_shapes_match_oracle(shape):
+    torch = need_gpu()
+    from paper_2502_04217_amd import csipm
+    w = _workload(shape, 3)
+    lam = ipm.lambda_rule(w.signal, w.observed)
+    beta, info = csipm.solve_small_batch(w.signal[None], w.observed[None], lambdas=[lam], tol=TOL)
+    ref = ipm.ipm_solve(w.signal, w.observed, lam, ipm.IPMOptions(tol=TOL))
+    err = rel2(beta[0].cpu().numpy(), ref.state.beta)
+    say("small", shape, "status", info[0, 0], "ipm", info[0, 1], ref.iters, "err", err)
+    assert info[0, 0] == 0 and abs(info[0, 1] - ref.iters) <= 1
+    assert err <= 1e-6   # both within tol of the limit: ten times the bar of the 1e-11 solves
+
+
+def test_tiled_batch_bit_identical_to_one_at_a_time():
+    torch = need_gpu()
+    from paper_2502_04217_amd import csipm
+    ws = [_workload((30, 28, 33), s) for s in range(5)]
+    sig, obs = np.stack([w.signal for w in ws]), np.stack([w.observed for w in ws])
+    beta, info = csipm.solve_small_batch(sig, obs, tol=1e-8)
+    for k in (0, 4):
+        b1, i1 = csipm.solve_small_batch(sig[k:k + 1], obs[k:k + 1], tol=1e-8)
+        assert torch.equal(b1[0], beta[k]) and np.array_equal(i1[0], info[k])

@@ -387,8 +387,8 @@ csipm_status csipm_mlp_adam(float* d_params, const float* d_grad, float* d_m, fl
                             void* hip_stream);
 /* One training step of the network on n_rec records: loss_grad at the
  * current parameters (loss to d_loss_out, gradient to d_grad), then adam
- * with step count t on d_params, d_m, d_v; the same kernels as those two
- * calls, queued in that order.  The moments are two arrays (m, v) and the
+ * with step count t on d_params, d_m, d_v; the same arithmetic as those two
+ * calls in that order.  The moments are two arrays (m, v) and the
  * step count is the caller's; d_scratch is as for loss_grad. */
 csipm_status csipm_mlp_train_step(float* d_params, float* d_m, float* d_v, int t, float lr, const float* d_feat,
                                   const float* d_rec, int n_rec, double* d_loss_out, float* d_grad, void* d_scratch,

@@ -1480,10 +1480,11 @@ csipm_status csipm_mlp_train_step(float* d_params, float* d_m, float* d_v, int t
                                   const float* d_rec, int n_rec, double* d_loss_out, float* d_grad, void* d_scratch,
                                   size_t scratch_bytes, void* hip_stream) {
   if (!d_params || !d_m || !d_v || t < 1 || !(lr > 0.0f)) return CSIPM_EINVAL;
-  const csipm_status st =
-      csipm_mlp_loss_grad(d_params, d_feat, d_rec, n_rec, d_loss_out, d_grad, d_scratch, scratch_bytes, hip_stream);
-  if (st != CSIPM_OK) return st;
-  return csipm_mlp_adam(d_params, d_grad, d_m, d_v, t, lr, hip_stream);
+  if (!d_feat || !d_rec || !d_loss_out || !d_grad || !d_scratch || n_rec < 1) return CSIPM_EINVAL;
+  if (scratch_bytes < csipm_mlp_scratch_bytes(n_rec)) return CSIPM_ENOMEM;
+  mlp_train_step(d_params, d_m, d_v, t, lr, d_feat, d_rec, n_rec, d_loss_out, d_grad, (double*)d_scratch,
+                 reinterpret_cast<hipStream_t>(hip_stream));
+  return hipGetLastError() == hipSuccess ? CSIPM_OK : CSIPM_EHIP;
 }
 
 csipm_status csipm_capture(csipm_ctx* c, int enable, float* d_feat, float* d_rec, int n_per_iter, int max_iters,

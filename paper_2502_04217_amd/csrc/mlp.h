@@ -61,10 +61,13 @@ void mlp_forward(const float* params, const float* feat, float* c, long long n, 
 void mlp_backward(const float* params, const float* feat, const float* dc, float* grad, int n, double* scratch,
                   hipStream_t s);
 // loss (double, device) and gradient (float, overwritten) over n records;
-// scratch holds ceil(n/128) * 1250 doubles
+// scratch holds ceil(n/64) * 1250 doubles
 void mlp_loss_grad(const float* params, const float* feat, const float* rec, int n, double* loss, float* grad,
                    double* scratch, hipStream_t s);
 void mlp_adam(float* params, const float* grad, float* m, float* v, int t, float lr, hipStream_t s);
+// mlp_loss_grad and mlp_adam, the step in the kernel that finishes the gradient
+void mlp_train_step(float* params, float* m, float* v, int t, float lr, const float* feat, const float* rec, int n,
+                    double* loss, float* grad, double* scratch, hipStream_t s);
 
 // Capture: records at coefficients idx_j = splitmix64(seed + j) mod n,
 // j < npick, from (p, q = K p) and the barrier diagonals; feat_all is the

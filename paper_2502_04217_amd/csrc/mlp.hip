@@ -16,7 +16,7 @@ constexpr int H1 = 32, H2 = 32, NIN = 4;
 constexpr int OW1 = 0, OB1 = OW1 + H1 * NIN, OW2 = OB1 + H1, OB2 = OW2 + H2 * H1, OW3 = OB2 + H2, OB3 = OW3 + H2;
 static_assert(OB3 + 1 == MLP_NP, "parameter layout");
 constexpr int RB = MLP_REC_PER_BLOCK;   // records per training workgroup
-constexpr int RP = RB + 1;      // padded LDS row
+constexpr int RP = RB + 4;      // padded LDS row of the records: the matrix operands' 16 rows and 4 records hit 64 banks
 constexpr int kGateBlocks = 1024;   // workgroups listing the coefficients where the correction acts
 
 __device__ __forceinline__ long long gtid() { return blockIdx.x * (long long)blockDim.x + threadIdx.x; }
@@ -42,32 +42,6 @@ __device__ __forceinline__ float tanh_fast(float x) {
 }
 __device__ __forceinline__ float softplusf(float x) { return fmaxf(x, 0.0f) + log1pf(__expf(-fabsf(x))); }
 __device__ __forceinline__ float sigmoidf(float x) { return 0.5f * (1.0f + tanh_fast(0.5f * x)); }
-
-__device__ __forceinline__ void load_params(const float* __restrict__ g, float* s) {
-  for (int i = threadIdx.x; i < MLP_NP; i += blockDim.x) s[i] = g[i];
-  __syncthreads();
-}
-
-// forward of one coefficient; returns o (pre-activation of the output)
-__device__ __forceinline__ float fwd1(const float* P, const float x[NIN], float h1[H1], float h2[H2]) {
-#pragma unroll
-  for (int i = 0; i < H1; ++i) {
-    float a = P[OB1 + i];
-#pragma unroll
-    for (int j = 0; j < NIN; ++j) a = fmaf(P[OW1 + i * NIN + j], x[j], a);
-    h1[i] = tanh_fast(a);
-  }
-  float o = P[OB3];
-#pragma unroll 4
-  for (int i = 0; i < H2; ++i) {
-    float a = P[OB2 + i];
-#pragma unroll
-    for (int j = 0; j < H1; ++j) a = fmaf(P[OW2 + i * H1 + j], h1[j], a);
-    h2[i] = tanh_fast(a);
-    o = fmaf(P[OW3 + i], h2[i], o);
-  }
-  return o;
-}
 
 // ------------------------------------------------ inference on MFMA --
 // Inference runs the two dense layers on the matrix cores
@@ -202,116 +176,155 @@ k_forward(const float* __restrict__ P, const float* __restrict__ feat, float* __
   }
 }
 
-// Per-block gradient partials over RB records.  mode 0: dc given (backward of
-// sum dc*c); mode 1: records, dc from the loss derivative, loss accumulated.
-// scratch[block][0..1248] gradient partials, scratch[block][1249] loss.
+// Gradient partials of RB records by four waves, 16 records each.  mode 0: dc
+// given (backward of sum dc*c); mode 1: records, dc from the loss derivative,
+// loss accumulated.  scratch[block][0..1248] gradient partials,
+// scratch[block][1249] loss.
+//
+// The forward pass and the back-propagation through W2 run on the FP32 matrix
+// cores in the register layout of the inference (a layer's output is the next
+// one's operand; W2^T's too).  The sums over the records are contractions as
+// well, with FP64 products and sums: D = L R^T on v_mfma_f64_16x16x4_f64
+// (lane l: A[l % 16][l / 16], B[l / 16][l % 16], D[l / 16 + 4 r][l % 16] in
+// register r) with the rows of L the deltas of layer 2, of layer 1 and of the
+// output, the rows of R the hidden values, the features and 1; 11 of the 25
+// 16 x 16 blocks of D hold gradients.  One thread per record and one thread per
+// parameter, each sum a chain of 64 FP64 products from LDS, took 38 us at
+// 4096 records (64 waves on the chip), and a training step 56; it takes 13.6
+// with this, the sliced k_grad_reduce and Adam in the latter.
+constexpr int kGradThreads = 256;
+struct GradBlock {
+  int l, r;   // row blocks of L (0, 1: layer 2; 2, 3: layer 1; 4: output) and R (0, 1: h1; 2, 3: h2; 4: features, 1)
+};
+__device__ constexpr GradBlock kGradBlocks[11] = {{0, 0}, {0, 1}, {1, 0}, {1, 1}, {0, 4}, {1, 4},
+                                                  {2, 4}, {3, 4}, {4, 2}, {4, 3}, {4, 4}};
+// parameter of element (i, j) of a block, -1: none
+__device__ __forceinline__ int grad_param(int lb, int rb, int i, int j) {
+  if (lb < 2) return rb < 2 ? OW2 + (16 * lb + i) * H1 + 16 * rb + j : (j == NIN ? OB2 + 16 * lb + i : -1);
+  if (lb < 4) {
+    const int n = 16 * (lb - 2) + i;
+    return j < NIN ? OW1 + n * NIN + j : (j == NIN ? OB1 + n : -1);
+  }
+  if (i != 0) return -1;
+  return rb < 4 ? OW3 + 16 * (rb - 2) + j : (j == NIN ? OB3 : -1);
+}
+typedef double d4_t __attribute__((ext_vector_type(4)));
+
 template <int MODE>
-__global__ void __launch_bounds__(RB)
+__global__ void __launch_bounds__(kGradThreads)
 k_grad_block(const float* __restrict__ params, const float* __restrict__ feat, const float* __restrict__ aux,
              int n, double* __restrict__ scratch) {
-  __shared__ float P[MLP_NP];
-  __shared__ float xs[NIN][RP], h1s[H1][RP], h2s[H2][RP], d1s[H1][RP], d2s[H2][RP], dos[RP];
-  load_params(params, P);
-  const int r = threadIdx.x;
-  const int idx = blockIdx.x * RB + r;
-  float x[NIN] = {0, 0, 0, 0}, h1[H1], h2[H2];
+  __shared__ float Lm[5 * 16][RP], Rm[5 * 16][RP];
+  __shared__ double es[kGradThreads / 64];
+  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, g = l >> 4, q = l & 15;
+  const int k = 16 * wv + q, idx = blockIdx.x * RB + k;   // the lane's record
+  const bool on = idx < n;
+  MfmaNet w;
+  load_net(params, w);
+  float w2t[2][8];   // rows 16m + q of W2^T, k-step s = 4t + r: W2[16t + 4g + r][16m + q]
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) w2t[m][s] = params[OW2 + (16 * (s >> 2) + 4 * g + (s & 3)) * H1 + 16 * m + q];
+  // the rows that stay zero, and the row of ones
+  for (int i = threadIdx.x; i < 15 * RB; i += kGradThreads) {
+    Lm[65 + i / RB][i % RB] = 0.0f;
+    if (i < 12 * RB) Rm[68 + i / RB][i % RB] = i < RB ? 1.0f : 0.0f;
+  }
+  const float xb = on ? feat[(long long)idx * NIN + g] : 0.0f;
+  Rm[64 + g][k] = xb;
+  f4_t h1[2], h2[2];
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    h1[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w1[m], xb, f4_t{w.b1[m][0], w.b1[m][1], w.b1[m][2], w.b1[m][3]}, 0,
+                                                 0, 0);
+    h2[m] = f4_t{w.b2[m][0], w.b2[m][1], w.b2[m][2], w.b2[m][3]};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      h1[m][r] = tanh_fast(h1[m][r]);
+      Rm[16 * m + 4 * g + r][k] = h1[m][r];
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 8; ++s)
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+      h2[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w2[m][s], h1[s >> 2][s & 3], h2[m], 0, 0, 0);
+  float o = 0.0f;
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      h2[m][r] = tanh_fast(h2[m][r]);
+      Rm[32 + 16 * m + 4 * g + r][k] = h2[m][r];
+      o = fmaf(w.w3[m][r], h2[m][r], o);
+    }
+  o += __shfl_xor(o, 16, 64);
+  o += __shfl_xor(o, 32, 64);
+  o += w.b3;
+  // every group of 16 lanes forms the output delta of its records
   float dout = 0.0f;
   double e = 0.0;
-  if (idx < n) {
-    const float4 f = reinterpret_cast<const float4*>(feat)[idx];
-    x[0] = f.x; x[1] = f.y; x[2] = f.z; x[3] = f.w;
-    const float o = fwd1(P, x, h1, h2);
+  if (on) {
     float dc;
     if constexpr (MODE == 0) {
       dc = aux[idx];
     } else {
       const float c = softplusf(o) + 1e-6f;
       const float* rc = aux + (long long)idx * MLP_REC;
-      const double u = rc[0], p = rc[1], L1 = rc[2], L2 = rc[3], S12 = rc[4], w = rc[5];
+      const double u = rc[0], p = rc[1], L1 = rc[2], L2 = rc[3], S12 = rc[4], wt = rc[5];
       const double D = L1 + S12;
       const double res = u - (double)c * p;
       const double a = (L1 * L1 + L2 * L2) / (D * D);
-      e = w * a * res * res;
-      dc = (float)(-2.0 * w * a * p * res);
+      if (g == 0) e = wt * a * res * res;
+      dc = (float)(-2.0 * wt * a * p * res);
     }
     dout = dc * sigmoidf(o);
-  } else {
-#pragma unroll
-    for (int i = 0; i < H1; ++i) h1[i] = 0.0f;
-#pragma unroll
-    for (int i = 0; i < H2; ++i) h2[i] = 0.0f;
   }
+  if (g == 0) Lm[64][k] = dout;
   // back-propagate to the hidden pre-activations
-  float d2[H2];
+  f4_t d2[2], d1[2];
 #pragma unroll
-  for (int i = 0; i < H2; ++i) d2[i] = dout * P[OW3 + i] * (1.0f - h2[i] * h2[i]);
-#pragma unroll 4
-  for (int j = 0; j < H1; ++j) {
-    float a = 0.0f;
+  for (int m = 0; m < 2; ++m) {
+    d1[m] = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int i = 0; i < H2; ++i) a = fmaf(d2[i], P[OW2 + i * H1 + j], a);
-    d1s[j][r] = a * (1.0f - h1[j] * h1[j]);
-  }
-#pragma unroll
-  for (int j = 0; j < NIN; ++j) xs[j][r] = x[j];
-#pragma unroll
-  for (int i = 0; i < H1; ++i) h1s[i][r] = h1[i];
-#pragma unroll
-  for (int i = 0; i < H2; ++i) {
-    h2s[i][r] = h2[i];
-    d2s[i][r] = d2[i];
-  }
-  dos[r] = dout;
-  __syncthreads();
-  double* out = scratch + (long long)blockIdx.x * (MLP_NP + 1);
-  for (int p = r; p < MLP_NP; p += RB) {
-    double g = 0.0;
-    if (p < OB1) {
-      const int i = p / NIN, j = p % NIN;
-      for (int k = 0; k < RB; ++k) g += (double)d1s[i][k] * (double)xs[j][k];
-    } else if (p < OW2) {
-      const int i = p - OB1;
-      for (int k = 0; k < RB; ++k) g += (double)d1s[i][k];
-    } else if (p < OB2) {
-      const int i = (p - OW2) / H1, j = (p - OW2) % H1;
-      for (int k = 0; k < RB; ++k) g += (double)d2s[i][k] * (double)h1s[j][k];
-    } else if (p < OW3) {
-      const int i = p - OB2;
-      for (int k = 0; k < RB; ++k) g += (double)d2s[i][k];
-    } else if (p < OB3) {
-      const int i = p - OW3;
-      for (int k = 0; k < RB; ++k) g += (double)dos[k] * (double)h2s[i][k];
-    } else {
-      for (int k = 0; k < RB; ++k) g += (double)dos[k];
+    for (int r = 0; r < 4; ++r) {
+      d2[m][r] = dout * w.w3[m][r] * (1.0f - h2[m][r] * h2[m][r]);
+      Lm[16 * m + 4 * g + r][k] = d2[m][r];
     }
-    out[p] = g;
   }
+#pragma unroll
+  for (int s = 0; s < 8; ++s)
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+      d1[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w2t[m][s], d2[s >> 2][s & 3], d1[m], 0, 0, 0);
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) Lm[32 + 16 * m + 4 * g + r][k] = d1[m][r] * (1.0f - h1[m][r] * h1[m][r]);
   e = wave_sum(e);
-  if (r == 0) out[MLP_NP] = e;
-}
-
-// Sums the block partials in block order.  accumulate: grad += (else =).
-__global__ void __launch_bounds__(256)
-k_grad_reduce(const double* __restrict__ scratch, int nblk, float* __restrict__ grad, double* __restrict__ loss,
-              int accumulate) {
-  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p <= MLP_NP; p += gridDim.x * blockDim.x) {
-    double g = 0.0;
-    for (int b = 0; b < nblk; ++b) g += scratch[(long long)b * (MLP_NP + 1) + p];
-    if (p < MLP_NP) {
-      grad[p] = accumulate ? (float)((double)grad[p] + g) : (float)g;
-    } else if (loss) {
-      *loss = g;
+  if (l == 0) es[wv] = e;
+  __syncthreads();
+  double* const out = scratch + (long long)blockIdx.x * (MLP_NP + 1);
+  for (int b = wv; b < 11; b += kGradThreads / 64) {
+    const int lb = kGradBlocks[b].l, rb = kGradBlocks[b].r;
+    d4_t acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < RB / 4; ++s)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Lm[16 * lb + q][4 * s + g], (double)Rm[16 * rb + q][4 * s + g],
+                                                 acc, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int pi = grad_param(lb, rb, g + 4 * r, q);
+      if (pi >= 0) out[pi] = acc[r];
     }
   }
+  if (threadIdx.x == 0) out[MLP_NP] = es[0] + es[1] + es[2] + es[3];
 }
 
-__global__ void __launch_bounds__(256)
-k_adam(float* __restrict__ params, const float* __restrict__ grad, float* __restrict__ m, float* __restrict__ v,
-       float b1t, float b2t, float lr) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= MLP_NP) return;
+__device__ __forceinline__ void adam_one(float* __restrict__ params, float g, float* __restrict__ m,
+                                         float* __restrict__ v, int i, float b1t, float b2t, float lr) {
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-  const float g = grad[i];
   const float mi = b1 * m[i] + (1.0f - b1) * g;
   const float vi = b2 * v[i] + (1.0f - b2) * g * g;
   m[i] = mi;
@@ -319,6 +332,50 @@ k_adam(float* __restrict__ params, const float* __restrict__ grad, float* __rest
   const float mh = mi / (1.0f - b1t);
   const float vh = vi / (1.0f - b2t);
   params[i] -= lr * mh / (sqrtf(vh) + eps);
+}
+
+struct AdamArgs {
+  float *params, *m, *v;   // params null: no step
+  float b1t, b2t, lr;
+};
+
+// Sums the block partials: each of the 8 slices of a workgroup's 256 threads
+// takes every eighth partial of its 32 parameters in order, then the slices in
+// order (one thread per parameter walking all partials took 17 us at 4096
+// records: 64 loads one after another).  accumulate: grad += (else =).  With
+// adam.params set, the parameter's Adam step follows in the same thread.
+constexpr int kReduceParams = 32;
+__global__ void __launch_bounds__(256)
+k_grad_reduce(const double* __restrict__ scratch, int nblk, float* __restrict__ grad, double* __restrict__ loss,
+              int accumulate, AdamArgs adam) {
+  __shared__ double part[8][kReduceParams];
+  const int slice = threadIdx.x / kReduceParams, j = threadIdx.x % kReduceParams;
+  const int p = blockIdx.x * kReduceParams + j;
+  double a = 0.0;
+  if (p <= MLP_NP) {
+#pragma unroll 8
+    for (int b = slice; b < nblk; b += 8) a += scratch[(long long)b * (MLP_NP + 1) + p];
+  }
+  part[slice][j] = a;
+  __syncthreads();
+  if (slice != 0 || p > MLP_NP) return;
+  double g = part[0][j];
+#pragma unroll
+  for (int k = 1; k < 8; ++k) g += part[k][j];
+  if (p < MLP_NP) {
+    const float gf = accumulate ? (float)((double)grad[p] + g) : (float)g;
+    grad[p] = gf;
+    if (adam.params) adam_one(adam.params, gf, adam.m, adam.v, p, adam.b1t, adam.b2t, adam.lr);
+  } else if (loss) {
+    *loss = g;
+  }
+}
+
+__global__ void __launch_bounds__(256)
+k_adam(float* __restrict__ params, const float* __restrict__ grad, float* __restrict__ m, float* __restrict__ v,
+       float b1t, float b2t, float lr) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < MLP_NP) adam_one(params, grad[i], m, v, i, b1t, b2t, lr);
 }
 
 __global__ void __launch_bounds__(256)
@@ -789,25 +846,41 @@ void mlp_forward(const float* params, const float* feat, float* c, long long n, 
   hipLaunchKernelGGL(k_forward, dim3(net_blocks(n)), dim3(64 * kNetWaves), 0, s, params, feat, c, n);
 }
 
+constexpr int kReduceBlocks = MLP_NP / kReduceParams + 1;   // (the loss is value MLP_NP)
+
 void mlp_backward(const float* params, const float* feat, const float* dc, float* grad, int n, double* scratch,
                   hipStream_t s) {
   const int nblk = (n + RB - 1) / RB;
-  hipLaunchKernelGGL((k_grad_block<0>), dim3(nblk), dim3(RB), 0, s, params, feat, dc, n, scratch);
-  hipLaunchKernelGGL(k_grad_reduce, dim3((MLP_NP + 256) / 256), dim3(256), 0, s, scratch, nblk, grad,
-                     (double*)nullptr, 1);
+  hipLaunchKernelGGL((k_grad_block<0>), dim3(nblk), dim3(kGradThreads), 0, s, params, feat, dc, n, scratch);
+  hipLaunchKernelGGL(k_grad_reduce, dim3(kReduceBlocks), dim3(256), 0, s, scratch, nblk, grad, (double*)nullptr, 1,
+                     AdamArgs{});
 }
 
 void mlp_loss_grad(const float* params, const float* feat, const float* rec, int n, double* loss, float* grad,
                    double* scratch, hipStream_t s) {
   const int nblk = (n + RB - 1) / RB;
-  hipLaunchKernelGGL((k_grad_block<1>), dim3(nblk), dim3(RB), 0, s, params, feat, rec, n, scratch);
-  hipLaunchKernelGGL(k_grad_reduce, dim3((MLP_NP + 256) / 256), dim3(256), 0, s, scratch, nblk, grad, loss, 0);
+  hipLaunchKernelGGL((k_grad_block<1>), dim3(nblk), dim3(kGradThreads), 0, s, params, feat, rec, n, scratch);
+  hipLaunchKernelGGL(k_grad_reduce, dim3(kReduceBlocks), dim3(256), 0, s, scratch, nblk, grad, loss, 0, AdamArgs{});
+}
+
+namespace {
+AdamArgs adam_args(float* params, float* m, float* v, int t, float lr) {
+  return AdamArgs{params, m, v, (float)std::pow(0.9, (double)t), (float)std::pow(0.999, (double)t), lr};
+}
+}  // namespace
+
+void mlp_train_step(float* params, float* m, float* v, int t, float lr, const float* feat, const float* rec, int n,
+                    double* loss, float* grad, double* scratch, hipStream_t s) {
+  const int nblk = (n + RB - 1) / RB;
+  hipLaunchKernelGGL((k_grad_block<1>), dim3(nblk), dim3(kGradThreads), 0, s, (const float*)params, feat, rec, n,
+                     scratch);
+  hipLaunchKernelGGL(k_grad_reduce, dim3(kReduceBlocks), dim3(256), 0, s, scratch, nblk, grad, loss, 0,
+                     adam_args(params, m, v, t, lr));
 }
 
 void mlp_adam(float* params, const float* grad, float* m, float* v, int t, float lr, hipStream_t s) {
-  const float b1t = (float)std::pow(0.9, (double)t);
-  const float b2t = (float)std::pow(0.999, (double)t);
-  hipLaunchKernelGGL(k_adam, dim3((MLP_NP + 255) / 256), dim3(256), 0, s, params, grad, m, v, b1t, b2t, lr);
+  const AdamArgs a = adam_args(params, m, v, t, lr);
+  hipLaunchKernelGGL(k_adam, dim3((MLP_NP + 255) / 256), dim3(256), 0, s, params, grad, m, v, a.b1t, a.b2t, lr);
 }
 
 template <typename T>

@@ -30,7 +30,7 @@
 // complex transforms of the whole spectrum, a pencil per thread in registers
 // (2 to 32 points) or direct DFTs in the workspace, one workgroup per problem,
 // a batch takes, in ms: 64 of 16^3 2.6 -> 2.0; 32 of 48 x 40 x 36 397 -> 8.8;
-// 64 of 32^3 29.6 -> 8.7; 16 of 64^3 about 500 -> 16; 50 of 24^3 38 -> 4.8.
+// 64 of 32^3 29.6 -> 8.7; 16 of 64^3 2810 -> 16; 50 of 24^3 38 -> 4.8.
 // Sixteen waves of 128 registers instead of eight of 232 spill and lose a
 // quarter.  A problem's result does not depend on the others in the batch: a
 // batch of one gives the same bits.

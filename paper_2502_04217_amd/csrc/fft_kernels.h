@@ -559,35 +559,35 @@ struct StridedGeom {
 // Tile shape of the strided (axis-1/2) passes per complex size w in bytes,
 // pencil length L, axis and direction: elements per thread E and pencils
 // per workgroup TM (LDS = TM L w, at most 1024 threads, TM a power of two).
-// Power-of-two pencils, chosen from measurements at 256^3: 8 elements per
-// thread for the FP64 axis-2 passes and the FP32 axis-1 forward pass, 16
-// otherwise; 128 KB tiles for axis 1 except the FP64 inverse pass (64 KB),
-// 64 KB for axis 2.  Pencils with odd factors take mixed_e elements.
+// The narrowest tile whose rows are whole 128-byte lines: small grids are
+// bound by the compute units that have a tile (64^3 in FP64 has 256 such
+// tiles and had 32 of 64 KB), large ones by loads in flight, which many small
+// workgroups on a compute unit keep up across each other's barriers.  The
+// forward pass of axis 1 also streams the vectors of its epilogue and takes
+// rows of 256 bytes.  apply_K in microseconds, tiles of 64 to 128 KB with 16
+// elements per thread in most passes against these, FP64 / FP32:
+//   64^3 33.6, 26.6 / 24.5, 21.5;  128^3 72, 47.6 / 68.4, 45.7;
+//   192^3 189, 113 / 177, 91.6;    256^3 382, 196 / 371, 181;
+//   384^3 1409, 739 / 1402, 707;   512^3 FP32 1664 / 1654;
+//   512 x 512 x 384 FP64 2490 / 2515, within what its runs differ by (80).
+// Rows of 256 bytes on the inverse pass of axis 1 take 3 % longer at 256^3
+// and 384^3 in FP32, on axis 2 50 % longer at 384^3; rows of 128 bytes on the
+// forward pass 4 % longer at 256^3 in FP32.  Pencils with odd factors take
+// mixed_e elements per thread, powers of two 8; of the FP32 pencils of 1024,
+// which would fill a workgroup of 8 pencils with that, all but the forward
+// pass of axis 1 take 16 (inverse pass at 1024 x 128 x 128 42 and 38 us).
 constexpr int strided_e(int w, int L, int axis, int dir) {
   if (odd_part(L) != 1) return mixed_e(L);
-  const int e = ((w == 16 && axis == 2) || (w == 8 && axis == 1 && dir < 0) ||
-                   (w == 16 && axis == 1 && dir > 0 && L >= 512))
-                    ? 8 : 16;
+  const int e = w == 8 && L == 1024 && !(axis == 1 && dir < 0) ? 16 : 8;
   return L < e ? L : e;
 }
-constexpr int strided_lds(int w, int axis, int dir, int L) {
-  return axis == 2 ? 65536 : (w == 16 && dir > 0 && L < 512 ? 65536 : 131072);
-}
-// TM is the power of two that the LDS budget gives (at most 64), raised
-// until each access is a run of at least 128 contiguous bytes (a whole
-// cache line) and the workgroup is whole waves (block reductions), within
-// 160 KB of LDS and 1024 threads.
+// TM gives rows of 128 or 256 bytes within 128 KB of LDS, and is raised
+// until the workgroup is whole waves (block reductions).
 constexpr int strided_tm(int w, int L, int axis, int dir) {
   const int nt = L / strided_e(w, L, axis, dir);
-  int tm = strided_lds(w, axis, dir, L) / (L * w);
-  if (tm > 64) tm = 64;
-  if (tm < 1) tm = 1;
-  int p = 1;
-  while (2 * p <= tm) p *= 2;
-  tm = p;
-  while (tm * w < 128 && 2 * tm * L * w <= 163840 && 2 * tm * nt <= 1024) tm *= 2;
+  int tm = (axis == 1 && dir < 0 ? 256 : 128) / w;
+  while (tm > 1 && (tm * L * w > 131072 || tm * nt > 1024)) tm >>= 1;
   while ((tm * nt) % 64 != 0 && 2 * tm * L * w <= 163840 && 2 * tm * nt <= 1024) tm *= 2;
-  while (tm * nt > 1024) tm >>= 1;
   return tm;
 }
 template <typename T, int L, int AX, int DIR>

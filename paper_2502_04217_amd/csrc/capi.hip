@@ -360,8 +360,8 @@ struct PcgOut {
 // writes x = alpha p.  On return r holds the recursive residual of x.
 //
 // One chunk of PCG iterations queued on c->s: K-apply of p (with the fused
-// direction update after the solve's first iteration), alpha, the update of
-// x, r, z and beta.  Finished iterations turn the rest of a chunk into
+// direction update after the solve's first iteration), the update of x, r and
+// z with alpha from the K-apply's partials, and beta.  Finished iterations turn the rest of a chunk into
 // no-ops through the device flag, so the host only synchronises once per
 // chunk.  If `capture` is set, p_0 and q_0 = K p_0 go to the capture hook.
 template <typename T>
@@ -379,9 +379,8 @@ void pcg_chunk(csipm_ctx* c, int chunk, bool first, T* xb, T* xz, const T* s1, c
   for (int k = 0; k < chunk; ++k) {
     const int nbk = op_K<T>(c, pb, pz, s1, s2, qb, qz, work, skip, first ? nullptr : &upd);
     if (first && capture) KT(c, "capture", capture_pair<T>(c, pb, pz, qb, qz, s1, s2));
-    KT(c, "fin_alpha", fin_alpha(c->partK, nbk, c->scal, c->flags, c->s));
     KT(c, PN(T, "cg_update"), cg_update<T>(xb, xz, pb, pz, qb, qz, rb, rz, zb, zz, s1, s2, pcc, c->scal, c->flags,
-                                          n, c->partV, first, c->s));
+                                          n, c->partV, first, c->s, c->partK, nbk));
     first = false;
     KT(c, "fin_rz", fin_rz(c->partV, nbv, c->scal, c->flags, c->s));
   }

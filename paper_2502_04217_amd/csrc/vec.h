@@ -45,8 +45,8 @@ int vec_blocks(long long n);
 
 template <typename T>
 void cg_update(T* xb, T* xz, const T* pb, const T* pz, const T* qb, const T* qz, T* rb, T* rz, T* zb, T* zz,
-               const T* s1, const T* s2, const float* c, const double* scal, const int* flags, long long n,
-               double* partial, bool first, hipStream_t s);
+               const T* s1, const T* s2, const float* c, double* scal, int* flags, long long n, double* partial,
+               bool first, hipStream_t s, const double* partpq = nullptr, int nbpq = 0);
 // conjugate residuals: p = z + beta p, q = w + beta q (p = z, q = w first),
 // partial q.P_c^{-1}q; and the finalize after w = K z (beta, alpha's numerator)
 template <typename T>

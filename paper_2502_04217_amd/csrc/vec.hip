@@ -65,16 +65,42 @@ __device__ __forceinline__ long long gstride() { return (long long)gridDim.x * b
 #define CSIPM_ALIGN(p) p = (decltype(p))__builtin_assume_aligned(p, 2 * sizeof(*(p)))
 
 // ------------------------------------------------------------------- PCG --
+__device__ __forceinline__ double fin_sum(const double* partial, int nb) {
+  double a = 0.0;
+  for (int i = threadIdx.x; i < nb; i += 256) a += partial[i];
+  return block_sum_256(a);
+}
+
+// alpha = r.z / p.Kp; true on the loss of positive definiteness in floating
+// point, which ends the solve
+__device__ __forceinline__ bool step_length(double pq, double rz, double& alpha) {
+  const bool bad = !(pq > 0.0) || !isfinite(pq);
+  alpha = bad ? 0.0 : rz / pq;
+  return bad;
+}
+__device__ __forceinline__ void store_step(double pq, double alpha, bool bad, double* scal, int* flags) {
+  scal[S_PQ] = pq;
+  scal[S_ALPHA] = alpha;
+  if (bad) {
+    flags[F_BREAK] = 1;
+    flags[F_DONE] = 1;
+  }
+}
+
 // x += alpha p (x = alpha p on the first iteration: x0 = 0 is never stored),
 // r -= alpha q, z = P_c^{-1} r, partial r.z.  A first iteration of a solve
-// that finished at initialisation writes x = 0 and nothing else.
+// that finished at initialisation writes x = 0 and nothing else.  With the
+// partials of p.Kp (nbpq > 0) every workgroup sums them, in the order of
+// k_fin_alpha, and the first one stores alpha: the reads come from the L2,
+// and one launch of an iteration's eight is gone (solve of 128^3 in FP64 5.65
+// -> 5.59 ms, of 64^3 2.13 -> 2.11; no difference at 256^3).
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_cg_update(T* __restrict__ xb, T* __restrict__ xz, const T* __restrict__ pb, const T* __restrict__ pz,
             const T* __restrict__ qb, const T* __restrict__ qz, T* __restrict__ rb, T* __restrict__ rz,
             T* __restrict__ zb, T* __restrict__ zz, const T* __restrict__ s1, const T* __restrict__ s2,
-            const float* __restrict__ c, const double* __restrict__ scal, const int* __restrict__ flags,
-            long long n, double* partial, int first) {
+            const float* __restrict__ c, double* scal, int* flags, long long n, double* partial, int first,
+            const double* partpq, int nbpq) {
   CSIPM_ALIGN(xb);
   CSIPM_ALIGN(xz);
   CSIPM_ALIGN(pb);
@@ -88,7 +114,16 @@ k_cg_update(T* __restrict__ xb, T* __restrict__ xz, const T* __restrict__ pb, co
   CSIPM_ALIGN(s1);
   CSIPM_ALIGN(s2);
 
-  if (flags[F_DONE]) {
+  bool done = flags[F_DONE] != 0;
+  double alpha = scal[S_ALPHA];
+  if (nbpq > 0 && !done) {
+    // (a workgroup that already sees F_DONE of the first one's breakdown here
+    // takes the same way as one that finds the breakdown itself)
+    const double pq = fin_sum(partpq, nbpq);
+    done = step_length(pq, scal[S_RZ], alpha);
+    if (blockIdx.x == 0 && threadIdx.x == 0) store_step(pq, alpha, done, scal, flags);
+  }
+  if (done) {
     if (first)
       CSIPM_PAIRS(n) {
         xb[i] = T(0);
@@ -96,7 +131,7 @@ k_cg_update(T* __restrict__ xb, T* __restrict__ xz, const T* __restrict__ pb, co
       }
     return;
   }
-  const T a = (T)scal[S_ALPHA];
+  const T a = (T)alpha;
   double acc = 0.0;
   using V = cx<T>;
   const V *PB = (const V*)pb, *PZ = (const V*)pz, *QB = (const V*)qb, *QZ = (const V*)qz, *S1 = (const V*)s1,
@@ -302,12 +337,6 @@ k_p_apply(const T* __restrict__ zb, const T* __restrict__ zz, const T* __restric
   }
 }
 
-__device__ __forceinline__ double fin_sum(const double* partial, int nb) {
-  double a = 0.0;
-  for (int i = threadIdx.x; i < nb; i += 256) a += partial[i];
-  return block_sum_256(a);
-}
-
 // Starts a PCG solve: rz0 from the partials (quantity 0) or, when
 // from_slot >= 0, from scal[from_slot]; with ref_slot >= 0 the second
 // quantity of the partials is summed into scal[ref_slot].
@@ -337,15 +366,9 @@ k_fin_alpha(const double* partial, int nb, double* scal, int* flags) {
   if (flags[F_DONE]) return;
   const double pq = fin_sum(partial, nb);
   if (threadIdx.x == 0) {
-    scal[S_PQ] = pq;
-    if (!(pq > 0.0) || !isfinite(pq)) {
-      // loss of positive definiteness in floating point: stop the solve
-      scal[S_ALPHA] = 0.0;
-      flags[F_BREAK] = 1;
-      flags[F_DONE] = 1;
-    } else {
-      scal[S_ALPHA] = scal[S_RZ] / pq;
-    }
+    double alpha;
+    const bool bad = step_length(pq, scal[S_RZ], alpha);
+    store_step(pq, alpha, bad, scal, flags);
   }
 }
 
@@ -802,39 +825,49 @@ k_ipm_advance(double* __restrict__ beta, double* __restrict__ z, double* __restr
   }
 }
 
-// Generic multi-value finalize: out[q] = op_q over partial[q*stride + 0..nb);
-// all quantities are reduced in one sweep.
-// one block of kFinThreads: at most two partials per thread and quantity for
-// the VEC_MAX_BLOCKS partials of a vector pass, loaded before they are combined
-constexpr int kFinThreads = 1024;
+// Generic multi-value finalize: out[q] = op_q over partial[q*stride + 0..nb).
+// One workgroup, bound by latency: kFinWaves / NQ waves take each quantity, so
+// that a wave's loads and its one reduction are all that lies in a row (16
+// waves that each reduced all ten quantities of a residual in turn took
+// 11.6 us at 256 partials, this 4.1; a solve
+// of 64^3 in FP64 2.26 -> 2.13 ms).
+constexpr int kFinWaves = 16;
 template <int NQ>
-__global__ void __launch_bounds__(kFinThreads)
+constexpr int fin_waves() { return kFinWaves / NQ > 1 ? kFinWaves / NQ : 1; }
+__device__ __forceinline__ double red_op(int op, double a, double b) {
+  return op == RED_SUM ? a + b : op == RED_MAX ? fmax(a, b) : fmin(a, b);
+}
+template <int NQ>
+__global__ void __launch_bounds__(64 * NQ * fin_waves<NQ>())
 k_fin_reduce(const double* partial, int nb, int stride, double* out, RedOps<NQ> ops) {
-  double a[NQ];
+  constexpr int W = fin_waves<NQ>(), U = 8;
+  const int wave = threadIdx.x >> 6, q = wave / W;
+  const int op = ops.op[q];
+  const double none = op == RED_SUM ? 0.0 : op == RED_MAX ? -INFINITY : INFINITY;
+  double a = none;
+  for (int i0 = (wave % W) * 64 + (threadIdx.x & 63); i0 < nb; i0 += U * W * 64) {
+    double x[U];
 #pragma unroll
-  for (int q = 0; q < NQ; ++q) a[q] = ops.op[q] == RED_SUM ? 0.0 : ops.op[q] == RED_MAX ? -INFINITY : INFINITY;
-  for (int i = threadIdx.x; i < nb; i += kFinThreads) {
-    double x[NQ];
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * W * 64;
+      x[u] = i < nb ? partial[q * stride + i] : none;
+    }
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) x[q] = partial[q * stride + i];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q)
-      a[q] = ops.op[q] == RED_SUM ? a[q] + x[q] : ops.op[q] == RED_MAX ? fmax(a[q], x[q]) : fmin(a[q], x[q]);
+    for (int u = 0; u < U; ++u) a = red_op(op, a, x[u]);
   }
-  constexpr int W = kFinThreads / 64;
-  __shared__ double red[NQ][W];
+  a = op == RED_SUM ? wave_sum(a) : op == RED_MAX ? wave_max(a) : wave_min(a);
+  if constexpr (W == 1) {
+    if ((threadIdx.x & 63) == 0) out[q] = a;
+  } else {
+    __shared__ double red[NQ * W];
+    if ((threadIdx.x & 63) == 0) red[wave] = a;
+    __syncthreads();
+    if (threadIdx.x < NQ) {
+      double x = red[threadIdx.x * W];
 #pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const double x = ops.op[q] == RED_SUM ? wave_sum(a[q]) : ops.op[q] == RED_MAX ? wave_max(a[q]) : wave_min(a[q]);
-    if ((threadIdx.x & 63) == 0) red[q][threadIdx.x >> 6] = x;
-  }
-  __syncthreads();
-  if (threadIdx.x < NQ) {
-    const int q = threadIdx.x;
-    double x = red[q][0];
-    for (int w = 1; w < W; ++w)
-      x = ops.op[q] == RED_SUM ? x + red[q][w] : ops.op[q] == RED_MAX ? fmax(x, red[q][w]) : fmin(x, red[q][w]);
-    out[q] = x;
+      for (int w = 1; w < W; ++w) x = red_op(ops.op[threadIdx.x], x, red[threadIdx.x * W + w]);
+      out[threadIdx.x] = x;
+    }
   }
 }
 
@@ -1034,10 +1067,10 @@ int vec_blocks(long long n) {
 
 template <typename T>
 void cg_update(T* xb, T* xz, const T* pb, const T* pz, const T* qb, const T* qz, T* rb, T* rz, T* zb, T* zz,
-               const T* s1, const T* s2, const float* c, const double* scal, const int* flags, long long n,
-               double* partial, bool first, hipStream_t s) {
+               const T* s1, const T* s2, const float* c, double* scal, int* flags, long long n, double* partial,
+               bool first, hipStream_t s, const double* partpq, int nbpq) {
   hipLaunchKernelGGL((k_cg_update<T>), VB, xb, xz, pb, pz, qb, qz, rb, rz, zb, zz, s1, s2, c, scal, flags, n,
-                     partial, first ? 1 : 0);
+                     partial, first ? 1 : 0, partpq, nbpq);
 }
 void fin_cg_start(const double* partial, int nb, int stride, double* scal, int* flags, double eta, double atol,
                   int maxit, int ref_slot, int from_slot, hipStream_t s) {
@@ -1104,7 +1137,7 @@ void ipm_resid(const double* beta, const double* z, const double* nu1, const dou
                const double* xi, double lam, long long n, double* partial, double* out8, bool logsum, hipStream_t s) {
   const int nb = vec_blocks(n);
   hipLaunchKernelGGL(k_ipm_resid, VB, beta, z, nu1, nu2, hb, xi, lam, n, partial, VEC_MAX_BLOCKS, logsum ? 1 : 0);
-  hipLaunchKernelGGL((k_fin_reduce<NRESID>), dim3(1), dim3(kFinThreads), 0, s, partial, nb, VEC_MAX_BLOCKS, out8,
+  hipLaunchKernelGGL((k_fin_reduce<NRESID>), dim3(1), dim3(64 * NRESID * fin_waves<NRESID>()), 0, s, partial, nb, VEC_MAX_BLOCKS, out8,
                      kResidRedOps);
 }
 void ipm_step(const double* beta, const double* z, const double* nu1, const double* nu2, const double* db,
@@ -1135,7 +1168,7 @@ void ipm_step(const double* beta, const double* z, const double* nu1, const doub
                      0.5 / (double)n);
   if (dsdn) {
     RedOps<1> ops{{RED_SUM}};
-    hipLaunchKernelGGL((k_fin_reduce<1>), dim3(1), dim3(kFinThreads), 0, s, partial + VEC_MAX_BLOCKS, nb, VEC_MAX_BLOCKS,
+    hipLaunchKernelGGL((k_fin_reduce<1>), dim3(1), dim3(64 * 1 * fin_waves<1>()), 0, s, partial + VEC_MAX_BLOCKS, nb, VEC_MAX_BLOCKS,
                        dsdn, ops);
   }
 }
@@ -1173,7 +1206,7 @@ void ipm_advance(double* beta, double* z, double* nu1, double* nu2, double* hbet
       CSIPM_ADV(float, false, ADV_RRES64, false, NewtonOut<float>{}, nullptr);
   }
 #undef CSIPM_ADV
-  hipLaunchKernelGGL((k_fin_reduce<NRESID>), dim3(1), dim3(kFinThreads), 0, s, partial, nb, VEC_MAX_BLOCKS, scal + S_RESID,
+  hipLaunchKernelGGL((k_fin_reduce<NRESID>), dim3(1), dim3(64 * NRESID * fin_waves<NRESID>()), 0, s, partial, nb, VEC_MAX_BLOCKS, scal + S_RESID,
                      kResidRedOps);
 }
 void add_f2d(double* db, double* dz, const float* eb, const float* ez, long long n, hipStream_t s) {
@@ -1188,11 +1221,11 @@ void ref_restart(const double* hb, const double* hz, const double* db, const dou
 }
 void fin_sum(const double* partial, int nb, double* out, hipStream_t s) {
   RedOps<1> ops{{RED_SUM}};
-  hipLaunchKernelGGL((k_fin_reduce<1>), dim3(1), dim3(kFinThreads), 0, s, partial, nb, VEC_MAX_BLOCKS, out, ops);
+  hipLaunchKernelGGL((k_fin_reduce<1>), dim3(1), dim3(64 * 1 * fin_waves<1>()), 0, s, partial, nb, VEC_MAX_BLOCKS, out, ops);
 }
 void fin_max(const double* partial, int nb, double* out, hipStream_t s) {
   RedOps<1> ops{{RED_MAX}};
-  hipLaunchKernelGGL((k_fin_reduce<1>), dim3(1), dim3(kFinThreads), 0, s, partial, nb, VEC_MAX_BLOCKS, out, ops);
+  hipLaunchKernelGGL((k_fin_reduce<1>), dim3(1), dim3(64 * 1 * fin_waves<1>()), 0, s, partial, nb, VEC_MAX_BLOCKS, out, ops);
 }
 template <typename T>
 void pinv_apply(const T* rb, const T* rz, T* zb, T* zz, const T* s1, const T* s2, const float* c, long long n,
@@ -1201,7 +1234,7 @@ void pinv_apply(const T* rb, const T* rz, T* zb, T* zz, const T* s1, const T* s2
   hipLaunchKernelGGL((k_pinv<T>), VB, rb, rz, zb, zz, s1, s2, c, n, partial);
   if (out) {
     RedOps<1> ops{{RED_SUM}};
-    hipLaunchKernelGGL((k_fin_reduce<1>), dim3(1), dim3(kFinThreads), 0, s, partial, nb, VEC_MAX_BLOCKS, out,
+    hipLaunchKernelGGL((k_fin_reduce<1>), dim3(1), dim3(64 * 1 * fin_waves<1>()), 0, s, partial, nb, VEC_MAX_BLOCKS, out,
                        ops);
   }
 }
@@ -1209,7 +1242,7 @@ void check_signal(const double* sig, const uint8_t* obs, long long n, double* pa
   const int nb = vec_blocks(n);
   hipLaunchKernelGGL(k_check_signal, VB, sig, obs, n, partial);
   RedOps<2> ops{{RED_SUM, RED_SUM}};
-  hipLaunchKernelGGL((k_fin_reduce<2>), dim3(1), dim3(kFinThreads), 0, s, partial, nb, VEC_MAX_BLOCKS, out2, ops);
+  hipLaunchKernelGGL((k_fin_reduce<2>), dim3(1), dim3(64 * 2 * fin_waves<2>()), 0, s, partial, nb, VEC_MAX_BLOCKS, out2, ops);
 }
 void zero_fill(const double* sig, const uint8_t* obs, double* out, long long n, hipStream_t s) {
   hipLaunchKernelGGL(k_zero_fill, VB, sig, obs, out, n);
@@ -1225,14 +1258,14 @@ void absmax(const double* a, long long n, double* partial, double* out, hipStrea
   const int nb = vec_blocks(n);
   hipLaunchKernelGGL(k_absmax, VB, a, n, partial);
   RedOps<1> ops{{RED_MAX}};
-  hipLaunchKernelGGL((k_fin_reduce<1>), dim3(1), dim3(kFinThreads), 0, s, partial, nb, VEC_MAX_BLOCKS, out, ops);
+  hipLaunchKernelGGL((k_fin_reduce<1>), dim3(1), dim3(64 * 1 * fin_waves<1>()), 0, s, partial, nb, VEC_MAX_BLOCKS, out, ops);
 }
 void lasso_cert(const double* beta, const double* g, double lam, long long n, double* partial, double* out,
                 hipStream_t s) {
   const int nb = vec_blocks(n);
   hipLaunchKernelGGL(k_lasso_cert, VB, beta, g, lam, n, partial);
   RedOps<NCERT_Q> ops{{RED_SUM, RED_SUM, RED_SUM, RED_SUM, RED_MAX, RED_MAX, RED_MAX}};
-  hipLaunchKernelGGL((k_fin_reduce<NCERT_Q>), dim3(1), dim3(kFinThreads), 0, s, partial, nb, VEC_MAX_BLOCKS, out,
+  hipLaunchKernelGGL((k_fin_reduce<NCERT_Q>), dim3(1), dim3(64 * NCERT_Q * fin_waves<NCERT_Q>()), 0, s, partial, nb, VEC_MAX_BLOCKS, out,
                      ops);
 }
 void diag_h(const double* bm_ext, double* out_ext, int n1, int n2, int n3, double mfrac, hipStream_t s) {
@@ -1244,8 +1277,8 @@ void diag_h(const double* bm_ext, double* out_ext, int n1, int n2, int n3, doubl
 
 #define CSIPM_VINST(T)                                                                                         \
   template void cg_update<T>(T*, T*, const T*, const T*, const T*, const T*, T*, T*, T*, T*, const T*,         \
-                             const T*, const float*, const double*, const int*, long long, double*, bool,      \
-                             hipStream_t);                                                                     \
+                             const T*, const float*, double*, int*, long long, double*, bool,                  \
+                             hipStream_t, const double*, int);                                                                     \
   template void newton_init<T>(const double*, const double*, const double*, const double*, const double*,     \
                                double, double, double*, double*, double*, double*, T*, T*,                     \
                                const float*, T*, T*, T*, T*, T*, T*, long long, double*, hipStream_t,          \

@@ -105,6 +105,9 @@ void newton_init(const double* beta, const double* z, const double* nu1, const d
                  const double* daz = nullptr);
 void set_f2d(double* db, double* dz, const float* eb, const float* ez, long long n, hipStream_t s);
 void fin_alpha(const double* partial, int nb, double* scal, int* flags, hipStream_t s);
+// scal and flags to pinned host memory, then seq to *hseq
+void export_scalars(const double* scal, const int* flags, double* hscal, int* hflags, unsigned* hseq, unsigned seq,
+                    hipStream_t s);
 void fin_rz(const double* partial, int nb, double* scal, int* flags, hipStream_t s);
 
 // beta = 0, z = z0, nu = lam/2, and G = -xi (H beta = 0)

@@ -986,6 +986,16 @@ k_obs_to_double(const uint8_t* __restrict__ obs, double* __restrict__ out, long 
   for (long long i = gtid(); i < n; i += gstride()) out[i] = obs[i] ? 1.0 : 0.0;
 }
 
+// The scalar and flag blocks to the host's pinned copy, then the call's number:
+// one wave, whose fence orders all its lanes' stores before the number.
+__global__ void __launch_bounds__(64)
+k_export(const double* scal, const int* flags, double* hscal, int* hflags, unsigned* hseq, unsigned seq) {
+  for (int i = threadIdx.x; i < S_COUNT; i += 64) hscal[i] = scal[i];
+  if (threadIdx.x < F_COUNT) hflags[threadIdx.x] = flags[threadIdx.x];
+  __threadfence_system();
+  if (threadIdx.x == 0) __hip_atomic_store(hseq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_fill(T* __restrict__ a, T v, long long n) {
@@ -1126,6 +1136,10 @@ void fin_cr_zw(const double* partial, int nb, double* scal, int* flags, bool fir
 }
 void fin_rz(const double* partial, int nb, double* scal, int* flags, hipStream_t s) {
   hipLaunchKernelGGL(k_fin_rz, dim3(1), dim3(256), 0, s, partial, nb, scal, flags);
+}
+void export_scalars(const double* scal, const int* flags, double* hscal, int* hflags, unsigned* hseq, unsigned seq,
+                    hipStream_t s) {
+  hipLaunchKernelGGL(k_export, dim3(1), dim3(64), 0, s, scal, flags, hscal, hflags, hseq, seq);
 }
 void ipm_init(double* beta, double* z, double* nu1, double* nu2, double* g, const double* xi, long long n, double z0,
               double lam, hipStream_t s) {

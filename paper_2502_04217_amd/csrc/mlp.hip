@@ -45,7 +45,7 @@ __device__ __forceinline__ float sigmoidf(float x) { return 0.5f * (1.0f + tanh_
 
 // ------------------------------------------------ inference on MFMA --
 // Inference runs the two dense layers on the matrix cores
-// (v_mfma_f32_16x16x4_f32, FP32 in, FP32 accumulate) with coefficients along
+// (the first, and both in training, on v_mfma_f32_16x16x4_f32) with coefficients along
 // the 16 columns and neurons along the rows.  Register layout of that MFMA
 // for lane l (g = l / 16, q = l % 16): A is 16x4 with lane l holding A[q][g],
 // B is 4x16 with lane l holding B[g][q], D is 16x16 with lane l holding
@@ -57,16 +57,18 @@ __device__ __forceinline__ float sigmoidf(float x) { return 0.5f * (1.0f + tanh_
 // layers.
 typedef float f4_t __attribute__((ext_vector_type(4)));
 
-struct MfmaNet {
+struct NetEdge {
   float w1[2];      // W1[16t + q][g]
-  float w2[2][8];   // output rows 16m + q, k-step s = 4t + r: W2[16m + q][16t + 4g + r]
   float b1[2][4];   // [t][r]: b1[16t + 4g + r]
   float b2[2][4];
   float w3[2][4];
   float b3;
 };
+struct MfmaNet : NetEdge {
+  float w2[2][8];   // output rows 16m + q, k-step s = 4t + r: W2[16m + q][16t + 4g + r]
+};
 
-__device__ __forceinline__ void load_net(const float* __restrict__ P, MfmaNet& w) {
+__device__ __forceinline__ void load_edge(const float* __restrict__ P, NetEdge& w) {
   const int l = threadIdx.x & 63, g = l >> 4, q = l & 15;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
@@ -78,30 +80,111 @@ __device__ __forceinline__ void load_net(const float* __restrict__ P, MfmaNet& w
       w.w3[t][r] = P[OW3 + 16 * t + 4 * g + r];
     }
   }
+  w.b3 = P[OB3];
+}
+__device__ __forceinline__ void load_net(const float* __restrict__ P, MfmaNet& w) {
+  const int l = threadIdx.x & 63, g = l >> 4, q = l & 15;
+  load_edge(P, w);
 #pragma unroll
   for (int m = 0; m < 2; ++m)
 #pragma unroll
     for (int s = 0; s < 8; ++s) w.w2[m][s] = P[OW2 + (16 * m + q) * H1 + 16 * (s >> 2) + 4 * g + (s & 3)];
-  w.b3 = P[OB3];
+}
+
+// The 32x32 layer of the inference takes its FP32 operands as sums of three
+// bf16 values (8 significand bits each, rounded to nearest, so 24 in all) and
+// forms the six products whose factors' places add up to two or less on
+// v_mfma_f32_16x16x32_bf16 with FP32 sums; the three left out are below 2^-24
+// of a product.  The FP32 matrix instructions run at the VALU's rate and in its
+// place: a pass over 2^21 records took VALU time plus FP32 MFMA time, of which
+// this layer was 27 of 76 us (76 -> 69 us with the accumulators in VGPRs and
+// six waves per SIMD, 56 with the three places, 54.7 with the tanh's factor in
+// the second layer's weights and their operands formed once per workgroup).
+// Error against 64 bits over weights of 0.1 to 3 and features of 0.3 to 10:
+// 4e-8 to 4e-7, 1 to 20 % below that of the FP32 instructions.
+// Register layout (lane l, g = l / 16, q = l % 16): A[q][8g + j], B[8g + j][q],
+// D[4g + r][q]; with contraction slot 8g + j the neuron 16 (j / 4) + 4g + j % 4
+// a layer's output is again the next operand.
+typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+typedef float f2_t __attribute__((ext_vector_type(2)));
+struct Split8 {
+  bf8_t p[3];   // places 0 (leading), 1 and 2
+};
+__device__ __forceinline__ void split8(const float x[8], Split8& o) {
+#pragma unroll
+  for (int j = 0; j < 8; j += 2) {
+    f2_t v = {x[j], x[j + 1]};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const bf2_t h = __builtin_convertvector(v, bf2_t);
+      o.p[k][j] = h[0];
+      o.p[k][j + 1] = h[1];
+      v -= __builtin_convertvector(h, f2_t);
+    }
+  }
 }
 
 // tanh without branches: 2 / (1 + exp(-2x)) - 1 with the hardware exp2 and
 // reciprocal (exp overflowing to +inf for large negative x gives -1); absolute
 // error ~2e-7, which is what the weighted sums of the next layer see.
-__device__ __forceinline__ float tanh_exp(float x) {
-  const float e = __builtin_amdgcn_exp2f(x * -2.8853900817779268f);
-  return fmaf(2.0f, __builtin_amdgcn_rcpf(1.0f + e), -1.0f);
+constexpr double kTanhScale = -2.8853900817779268;   // -2 log2(e)
+__device__ __forceinline__ float tanh_scaled(float y) {   // tanh(x) of y = kTanhScale x
+  return fmaf(2.0f, __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(y)), -1.0f);
+}
+
+struct InferNet : NetEdge {
+  Split8 w2[2];   // output rows 16m + q, times kTanhScale (as b2): the second layer's sums are tanh_scaled's argument
+};
+// The operands of W2 for the 64 lanes, [m][place][lane][8], formed by nthr
+// threads in st: a wave with a few chunks would spend as long on forming its
+// own as on a chunk.
+constexpr int kStage = 2 * 3 * 64 * 8;
+__device__ __forceinline__ void stage_net(const float* __restrict__ P, __bf16* st, int tid, int nthr) {
+#pragma unroll 2
+  for (int e = tid; e < 128; e += nthr) {
+    const int m = e >> 6, l = e & 63, g = l >> 4, q = l & 15;
+    float x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = P[OW2 + (16 * m + q) * H1 + 16 * (j >> 2) + 4 * g + (j & 3)];
+    bf8_t h[3];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      // (scaled and split in FP64: the three places keep 26 bits of the product;
+      // an infinite weight acts as the largest bf16, so that no place overflows)
+      constexpr double big = 0x1.fep127;
+      double v = kTanhScale * x[j];
+      if (fabs(v) > big) v = copysign(big, v);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        h[k][j] = (__bf16)(float)v;
+        v -= (double)(float)h[k][j];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) reinterpret_cast<bf8_t*>(st)[(m * 3 + k) * 64 + l] = h[k];
+  }
+}
+__device__ __forceinline__ void load_infer(const float* __restrict__ P, const __bf16* st, InferNet& w) {
+  load_edge(P, w);
+  const int l = threadIdx.x & 63;
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w.w2[m].p[k] = reinterpret_cast<const bf8_t*>(st)[(m * 3 + k) * 64 + l];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w.b2[m][r] *= (float)kTanhScale;
+  }
 }
 
 // Output pre-activation o for a chunk of 64 coefficients, lane l holding the
 // four features of coefficient l.  The chunk is four tiles of 16
 // coefficients; lane (g, q) takes feature g of coefficient 16t + q of tile t
 // (staged through `lds`, this wave's 256 floats) and receives o of
-// coefficient l.  The four tiles go through each layer together, so the
-// matrix core sees eight independent accumulation chains in the 32x32 layer
-// while the VALU works on the tanh of the other tiles.
+// coefficient l.  TB tiles go through each layer together; the matrix core
+// works on one wave's 32x32 layer while the VALU forms others' tanh.
 template <int TB>
-__device__ __forceinline__ float net_chunk(const MfmaNet& w, float* lds, const float x[NIN]) {
+__device__ __forceinline__ float net_chunk(const InferNet& w, float* lds, const float x[NIN]) {
   const int l = threadIdx.x & 63, g = l >> 4, q = l & 15;
   reinterpret_cast<float4*>(lds)[l] = make_float4(x[0], x[1], x[2], x[3]);
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -126,23 +209,33 @@ __device__ __forceinline__ float net_chunk(const MfmaNet& w, float* lds, const f
 #pragma unroll
       for (int m = 0; m < 2; ++m) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) h1[t][m][r] = tanh_exp(h1[t][m][r]);
+        for (int r = 0; r < 4; ++r) h1[t][m][r] = tanh_scaled(h1[t][m][r] * (float)kTanhScale);
         h2[t][m] = f4_t{w.b2[m][0], w.b2[m][1], w.b2[m][2], w.b2[m][3]};
       }
+    Split8 hs[TB];
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
+    for (int t = 0; t < TB; ++t) {
+      const float v[8] = {h1[t][0][0], h1[t][0][1], h1[t][0][2], h1[t][0][3],
+                          h1[t][1][0], h1[t][1][1], h1[t][1][2], h1[t][1][3]};
+      split8(v, hs[t]);
+    }
+    // (the smallest products first)
+#pragma unroll
+    for (int s = 5; s >= 0; --s) {
+      const int i = s == 2 || s == 4 ? 1 : s == 5 ? 2 : 0, j = s == 1 || s == 4 ? 1 : s == 3 ? 2 : 0;
 #pragma unroll
       for (int t = 0; t < TB; ++t)
 #pragma unroll
         for (int m = 0; m < 2; ++m)
-          h2[t][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w2[m][s], h1[t][s >> 2][s & 3], h2[t][m], 0, 0, 0);
+          h2[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.w2[m].p[i], hs[t].p[j], h2[t][m], 0, 0, 0);
+    }
 #pragma unroll
     for (int t = 0; t < TB; ++t) {
       float a = 0.0f;
 #pragma unroll
       for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) a = fmaf(w.w3[m][r], tanh_exp(h2[t][m][r]), a);
+        for (int r = 0; r < 4; ++r) a = fmaf(w.w3[m][r], tanh_scaled(h2[t][m][r]), a);
       a += __shfl_xor(a, 16, 64);
       a += __shfl_xor(a, 32, 64);
       o[t0 + t] = a;
@@ -152,16 +245,21 @@ __device__ __forceinline__ float net_chunk(const MfmaNet& w, float* lds, const f
   return mine + w.b3;
 }
 
-// tiles that go through a layer together (register use against overlap)
-constexpr int kNetTiles = 2;
+// tiles that go through a layer together, and the waves per SIMD k_forward is
+// held to (2^21 records): one tile and five waves 56.5 us, two or four tiles
+// and the four or three waves their registers leave 59, six waves with spills 82
+constexpr int kNetTiles = 1;
 
 constexpr int kNetWaves = 4;   // waves per inference workgroup
 
-__global__ void __launch_bounds__(64 * kNetWaves)
+__global__ void __launch_bounds__(64 * kNetWaves, 5)
 k_forward(const float* __restrict__ P, const float* __restrict__ feat, float* __restrict__ c, long long n) {
   __shared__ float lds[kNetWaves][64 * NIN];
-  MfmaNet w;
-  load_net(P, w);
+  __shared__ __align__(16) __bf16 st[kStage];
+  stage_net(P, st, threadIdx.x, 64 * kNetWaves);
+  __syncthreads();
+  InferNet w;
+  load_infer(P, st, w);
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const long long nch = (n + 63) / 64;
   for (long long ch = blockIdx.x * (long long)kNetWaves + wv; ch < nch; ch += (long long)gridDim.x * kNetWaves) {
@@ -485,14 +583,17 @@ __device__ __forceinline__ bool state_features(const double* __restrict__ beta, 
 // relative).  The network runs on the matrix cores for every 64-coefficient
 // chunk that holds an active coefficient; set[chunk] records which chunks
 // those are (where c may differ from 1).
-__global__ void __launch_bounds__(64 * kNetWaves)
+__global__ void __launch_bounds__(64 * kNetWaves, 4)
 k_correction_state(const double* __restrict__ beta, const double* __restrict__ z, const double* __restrict__ nu1,
                    const double* __restrict__ nu2, const double* __restrict__ diagH,
                    const double* __restrict__ meanlog, double mscale, const double* __restrict__ bmax,
                    const float* __restrict__ P, float* __restrict__ c, long long n, uint32_t* __restrict__ set) {
   __shared__ float lds[kNetWaves][64 * NIN];
-  MfmaNet w;
-  load_net(P, w);
+  __shared__ __align__(16) __bf16 st[kStage];
+  stage_net(P, st, threadIdx.x, 64 * kNetWaves);
+  __syncthreads();
+  InferNet w;
+  load_infer(P, st, w);
   const double ml = *meanlog * mscale;
   const double ibm = *bmax > 0.0 ? 1.0 / *bmax : 1.0;
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -512,7 +613,7 @@ k_correction_state(const double* __restrict__ beta, const double* __restrict__ z
 // One active chunk of k_correction_patch: c of its 64 coefficients, the
 // patched PCG start where c acts, and the changes of the start sums.
 template <typename TC>
-__device__ __forceinline__ void patch_chunk(const MfmaNet& w, float* lds, const double* __restrict__ beta,
+__device__ __forceinline__ void patch_chunk(const InferNet& w, float* lds, const double* __restrict__ beta,
                                             const double* __restrict__ z, const double* __restrict__ nu1,
                                             const double* __restrict__ nu2, const double* __restrict__ diagH,
                                             double ml, double ibm, float* __restrict__ c, uint32_t* __restrict__ set,
@@ -566,7 +667,7 @@ __device__ __forceinline__ void patch_chunk(const MfmaNet& w, float* lds, const 
 // float the FP64 h and Sigma are hb64/hz64 and s164/s264 (null for a system
 // solved without refinement, whose h.P^{-1}h is not used).
 template <typename TC>
-__global__ void __launch_bounds__(64 * kNetWaves)
+__global__ void __launch_bounds__(64 * kNetWaves, 2)
 k_correction_patch(const double* __restrict__ beta, const double* __restrict__ z, const double* __restrict__ nu1,
                    const double* __restrict__ nu2, const double* __restrict__ diagH,
                    const double* __restrict__ meanlog, double mscale, const double* __restrict__ bmax,
@@ -579,7 +680,8 @@ k_correction_patch(const double* __restrict__ beta, const double* __restrict__ z
   constexpr bool F64 = std::is_same<TC, double>::value;
   __shared__ float lds[kNetWaves][64 * NIN];
   __shared__ double red[2][kNetWaves];
-  MfmaNet w;
+  __shared__ __align__(16) __bf16 st[kNetWaves][kStage];   // (a wave without an active chunk forms none)
+  InferNet w;
   bool loaded = false;
   const double ml = *meanlog * mscale;
   const double ibm = *bmax > 0.0 ? 1.0 / *bmax : 1.0;
@@ -613,7 +715,11 @@ k_correction_patch(const double* __restrict__ beta, const double* __restrict__ z
         continue;
       }
       if (!loaded) {
-        load_net(P, w);
+        stage_net(P, st[wv], l, 64);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        load_infer(P, st[wv], w);
         loaded = true;
       }
       patch_chunk<TC>(w, lds[wv], beta, z, nu1, nu2, diagH, ml, ibm, c, set, n, ch, l, h64, s1c, s2c, rb, rz, pb,

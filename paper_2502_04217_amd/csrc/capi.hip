@@ -239,6 +239,10 @@ const Twiddles<float>& tw<float>(csipm_ctx* c) { return c->T32; }
 template <typename T>
 void op_H(csipm_ctx* c, const T* in, T* out, T* work, bool ext = false) {
   const Grid& g = c->g;
+  if (ext && cube_pass(g)) {
+    KT(c, PN(T, "apply_H"), launch_cube<T>(g, CUBE_H, in, out, c->mask, tw<T>(c), nullptr, c->s));
+    return;
+  }
   KT(c, PN(T, "axis1_inv"), launch_axis12<T>(g, 1, +1, in, work, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s, ext));
   KT(c, PN(T, "axis2_inv"), launch_axis12<T>(g, 2, +1, work, work, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s));
   KT(c, PN(T, "axis3"), launch_axis3<T>(g, A3_FULL, work, work, c->mask, tw<T>(c), nullptr, c->s));
@@ -251,6 +255,10 @@ void op_H(csipm_ctx* c, const T* in, T* out, T* work, bool ext = false) {
 template <typename T>
 void op_A(csipm_ctx* c, const T* in, T* x, T* work) {
   const Grid& g = c->g;
+  if (cube_pass(g)) {
+    launch_cube<T>(g, CUBE_A, in, x, nullptr, tw<T>(c), nullptr, c->s);
+    return;
+  }
   launch_axis12<T>(g, 1, +1, in, work, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s, true);
   launch_axis12<T>(g, 2, +1, work, work, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s);
   launch_axis3<T>(g, A3_C2R, work, x, nullptr, tw<T>(c), nullptr, c->s);
@@ -260,6 +268,10 @@ void op_A(csipm_ctx* c, const T* in, T* x, T* work) {
 template <typename T>
 void op_At(csipm_ctx* c, const T* x, T* out, T* work, bool ext = false) {
   const Grid& g = c->g;
+  if (ext && cube_pass(g)) {
+    launch_cube<T>(g, CUBE_AT, x, out, nullptr, tw<T>(c), nullptr, c->s);
+    return;
+  }
   launch_axis3<T>(g, A3_R2C, x, work, nullptr, tw<T>(c), nullptr, c->s);
   launch_axis12<T>(g, 2, -1, work, work, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s);
   launch_axis12<T>(g, 1, -1, work, out, tw<T>(c), EPI_NONE, nullptr, nullptr, c->s, ext);
@@ -273,6 +285,10 @@ int op_K(csipm_ctx* c, const T* pb, const T* pz, const T* s1, const T* s2, T* qb
   const Grid& g = c->g;
   const int ps = (int)k_partials(g.n1, g.n2, g.n3);
   EpiArgs<T> ka{KArgs<T>{pb, pz, s1, s2, qb, qz, u ? *u : PUpd<T>{}}, RArgs{}, c->partK, ps};
+  if (ext && cube_pass(g)) {
+    KT(c, PN(T, "apply_K"), launch_cube<T>(g, CUBE_K, pb, (T*)nullptr, c->mask, tw<T>(c), &ka, c->s));
+    return 1;
+  }
   const int nb5 = axis12_blocks(g, 1, (int)sizeof(cx<T>), -1);
   // (the passes that apply the direction update are timed under their own names)
   KT(c, u ? PN(T, "axis1_inv_P") : PN(T, "axis1_inv"),

@@ -281,6 +281,15 @@ void launch_axis3(const Grid& g, int mode, const T* src, T* dst, const uint32_t*
 // inverse / -1 forward), those of the m = 0 plane included; for the axis-1
 // forward pass also its partial count
 int axis12_blocks(const Grid& g, int axis, int elem_bytes, int dir);
+// An operator apply of a small grid (cube_pass) as one launch of one workgroup,
+// its reduction as one partial (fft_cube.hip): A, A^T, H or K (ea) on the
+// caller's arrays.
+constexpr int kCubeMax = 6144;   // points (measured in fft_cube.hip)
+enum CubeOp { CUBE_A, CUBE_AT, CUBE_H, CUBE_K };
+bool cube_pass(const Grid& g);
+template <typename T>
+void launch_cube(const Grid& g, CubeOp op, const T* in, T* out, const uint32_t* mask, const Twiddles<T>& tw,
+                 const EpiArgs<T>* ea, hipStream_t s);
 // whether the FFT passes have kernels for extent N on `axis` (1, 2: pencils
 // of length N; 3: half length N/2 for an even N, full length for an odd N,
 // whose rows are transformed two by two): every N = 2^a 3^b 5^c 7^d in

@@ -1,7 +1,7 @@
 """Throughput of many small independent solves: one after another against
 csipm_solve_batch (each problem on its own stream, solves on a pool of host
-threads) and against csipm_solve_small_batch (one kernel, one workgroup per
-problem).  The paper's synthetic problem at a small grid, seeds
+threads) and against csipm_solve_small_batch (one kernel, a workgroup or a
+team of workgroups per problem).  The paper's synthetic problem at a small grid, seeds
 0..count-1.
 
     python -m paper_2502_04217_amd.batch_throughput [--grid 16] [--count 64] [--threads 1 2 4 8]

@@ -163,18 +163,20 @@ void kt_end(csipm_ctx* c, size_t e) {
 // kernel name with the precision of T
 #define PN(T, s) (sizeof(T) == 8 ? s ".f64" : s ".f32")
 
-// Reads the device scalar and flag blocks once all queued work is done.  A
-// kernel stores them to pinned host memory with the read's number behind
-// them, and the host polls that number: two copies and the runtime's wait
+HostCopy host_copy(csipm_ctx* c) { return HostCopy{c->hscal, c->hflags, c->hseq}; }
+
+// Waits for the host's copy of the device scalar and flag blocks under the next
+// number, which a queued kernel stores to pinned host memory with the number
+// behind them.  The host polls that number: two copies and the runtime's wait
 // left the GPU idle for 30 to 40 us at each of a solve's reads (solve of
-// 64^3 in FP64 2.10 -> 1.90 to 2.00 ms, in FP32 1.91 -> 1.65).  A
-// wait beyond kPollUs, as on large grids, and the last read of an entry point
-// (last: the stream is idle when it returns) take the runtime's wait, which
-// also reports a failed kernel.
+// 64^3 in FP64 2.10 -> 1.90 to 2.00 ms, in FP32 1.91 -> 1.65).  A wait beyond
+// kPollUs, as on large grids, and the last read of an entry point (last: the
+// stream is idle when it returns) take the runtime's wait, which also reports a
+// failed kernel.
 constexpr int kPollUs = 1000;
-csipm_status sync_scalars(csipm_ctx* c, const char* where, bool last = false) {
-  const unsigned seq = ++c->seq;
-  export_scalars(c->scal, c->flags, c->hscal, c->hflags, c->hseq, seq, c->s);
+unsigned next_seq(csipm_ctx* c) { return c->seq + 1 ? c->seq + 1 : 1; }
+csipm_status wait_scalars(csipm_ctx* c, const char* where, bool last = false) {
+  const unsigned seq = c->seq = next_seq(c);
   hipError_t e = hipGetLastError();
   const auto t0 = std::chrono::steady_clock::now();
   bool seen = false;
@@ -187,6 +189,11 @@ csipm_status sync_scalars(csipm_ctx* c, const char* where, bool last = false) {
   if (!seen && e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) return fail(c, CSIPM_EHIP, std::string(where) + ": " + hipGetErrorString(e));
   return CSIPM_OK;
+}
+// Reads the blocks once all queued work is done, by a kernel of its own.
+csipm_status sync_scalars(csipm_ctx* c, const char* where, bool last = false) {
+  export_scalars(c->scal, c->flags, host_copy(c), next_seq(c), c->s);
+  return wait_scalars(c, where, last);
 }
 
 // partial sums of one K-apply: one per workgroup of the axis-1 forward pass
@@ -416,7 +423,7 @@ void pcg_chunk(csipm_ctx* c, int chunk, bool first, T* xb, T* xz, const T* s1, c
     KT(c, PN(T, "cg_update"), cg_update<T>(xb, xz, pb, pz, qb, qz, rb, rz, zb, zz, s1, s2, pcc, c->scal, c->flags,
                                           n, c->partV, first, c->s, c->partK, nbk));
     first = false;
-    KT(c, "fin_rz", fin_rz(c->partV, nbv, c->scal, c->flags, c->s));
+    KT(c, "fin_rz", fin_rz(c->partV, nbv, c->scal, c->flags, c->s, k + 1 == chunk ? host_copy(c) : HostCopy{}));
   }
 }
 
@@ -478,7 +485,7 @@ csipm_status pcg(csipm_ctx* c, T* xb, T* xz, const T* s1, const T* s2, const flo
       pcg_chunk<T>(c, chunk, first, xb, xz, s1, s2, pcc, capture);
     }
     first = false;
-    csipm_status st = sync_scalars(c, "pcg");
+    csipm_status st = wait_scalars(c, "pcg");   // (stored by the chunk's last kernel)
     if (st != CSIPM_OK) return st;
     if (c->hflags[F_DONE]) break;
     chunk = std::min(chunk * 2, 16);
@@ -1291,8 +1298,8 @@ csipm_status csipm_solve(csipm_ctx* c, const csipm_options* opts, csipm_info* in
        ipm_advance(c->beta, c->z, c->nu1, c->nu2, c->hb, c->dxb, c->dxz, d32b, d32z,
                    src == HD_DIRECT ? c->rb : nullptr, c->rb, src == HD_RRES32 ? c->frb : nullptr, lam, smu, c->scal, n,
                    c->partV, need_rel, c->s, dab, daz, fuse_kind != NEXT_NONE ? &nx : nullptr,
-                   learned ? c->pc_act : nullptr));
-    st = sync_scalars(c, "advance");
+                   learned ? c->pc_act : nullptr, c->flags, host_copy(c)));
+    st = wait_scalars(c, "advance");   // (stored by the update's finalize)
     if (st != CSIPM_OK) return st;
     r = read_resid(c);
     next_kind = fuse_kind;

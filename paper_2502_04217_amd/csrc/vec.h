@@ -39,7 +39,14 @@ enum ScalarSlot {
   S_COUNT = 64
 };
 // int slots of the device flag block
-enum FlagSlot { F_DONE = 0, F_IT = 1, F_MAXIT = 2, F_BREAK = 3, F_COUNT = 8 };
+// (F_SEQ: the number of the host's last read of the two blocks)
+enum FlagSlot { F_DONE = 0, F_IT = 1, F_MAXIT = 2, F_BREAK = 3, F_SEQ = 4, F_COUNT = 8 };
+// the host's pinned copy of the scalar and flag blocks (seq null: none)
+struct HostCopy {
+  double* scal = nullptr;
+  int* flags = nullptr;
+  unsigned* seq = nullptr;
+};
 
 int vec_blocks(long long n);
 
@@ -105,10 +112,10 @@ void newton_init(const double* beta, const double* z, const double* nu1, const d
                  const double* daz = nullptr);
 void set_f2d(double* db, double* dz, const float* eb, const float* ez, long long n, hipStream_t s);
 void fin_alpha(const double* partial, int nb, double* scal, int* flags, hipStream_t s);
-// scal and flags to pinned host memory, then seq to *hseq
-void export_scalars(const double* scal, const int* flags, double* hscal, int* hflags, unsigned* hseq, unsigned seq,
-                    hipStream_t s);
-void fin_rz(const double* partial, int nb, double* scal, int* flags, hipStream_t s);
+// scal and flags to the host's copy under the number seq
+void export_scalars(const double* scal, int* flags, const HostCopy& h, unsigned seq, hipStream_t s);
+// (with h the host's read after the kernel, under the next number)
+void fin_rz(const double* partial, int nb, double* scal, int* flags, hipStream_t s, const HostCopy& h = HostCopy{});
 
 // beta = 0, z = z0, nu = lam/2, and G = -xi (H beta = 0)
 void ipm_init(double* beta, double* z, double* nu1, double* nu2, double* g, const double* xi, long long n, double z0,
@@ -142,8 +149,8 @@ void ipm_step(const double* beta, const double* z, const double* nu1, const doub
 void ipm_advance(double* beta, double* z, double* nu1, double* nu2, double* hbeta, const double* db,
                  const double* dz, const float* db32, const float* dz32, const double* hd,
                  const double* rres, const float* rres32, double lam, double smu, double* scal, long long n,
-                 double* partial, bool logsum, hipStream_t s, const double* dab = nullptr,
-                 const double* daz = nullptr, const NextSystem* next = nullptr, uint32_t* act = nullptr);
+                 double* partial, bool logsum, hipStream_t s, const double* dab,
+                 const double* daz, const NextSystem* next, uint32_t* act, int* flags, const HostCopy& h);
 
 void add_f2d(double* db, double* dz, const float* eb, const float* ez, long long n, hipStream_t s);
 // FP32 restart of a further inner solve from H d_beta (hd): r32, z32 = p32 =

@@ -81,10 +81,7 @@ __device__ __forceinline__ bool step_length(double pq, double rz, double& alpha)
 __device__ __forceinline__ void store_step(double pq, double alpha, bool bad, double* scal, int* flags) {
   scal[S_PQ] = pq;
   scal[S_ALPHA] = alpha;
-  if (bad) {
-    flags[F_BREAK] = 1;
-    flags[F_DONE] = 1;
-  }
+  if (bad) flags[F_BREAK] = 1;
 }
 
 // x += alpha p (x = alpha p on the first iteration: x0 = 0 is never stored),
@@ -93,7 +90,10 @@ __device__ __forceinline__ void store_step(double pq, double alpha, bool bad, do
 // partials of p.Kp (nbpq > 0) every workgroup sums them, in the order of
 // k_fin_alpha, and the first one stores alpha: the reads come from the L2,
 // and one launch of an iteration's eight is gone (solve of 128^3 in FP64 5.65
-// -> 5.59 ms, of 64^3 2.13 -> 2.11; no difference at 256^3).
+// -> 5.59 ms, of 64^3 2.13 -> 2.11; no difference at 256^3).  A breakdown, which
+// every workgroup finds for itself from the same bits, is stored as F_BREAK
+// alone: F_DONE, which every wave of this launch reads when it starts, is
+// written by the k_fin_rz that follows.
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_cg_update(T* __restrict__ xb, T* __restrict__ xz, const T* __restrict__ pb, const T* __restrict__ pz,
@@ -115,10 +115,10 @@ k_cg_update(T* __restrict__ xb, T* __restrict__ xz, const T* __restrict__ pb, co
   CSIPM_ALIGN(s2);
 
   bool done = flags[F_DONE] != 0;
-  double alpha = scal[S_ALPHA];
-  if (nbpq > 0 && !done) {
-    // (a workgroup that already sees F_DONE of the first one's breakdown here
-    // takes the same way as one that finds the breakdown itself)
+  double alpha = 0.0;
+  if (nbpq == 0) {
+    alpha = scal[S_ALPHA];
+  } else if (!done) {
     const double pq = fin_sum(partpq, nbpq);
     done = step_length(pq, scal[S_RZ], alpha);
     if (blockIdx.x == 0 && threadIdx.x == 0) store_step(pq, alpha, done, scal, flags);
@@ -369,6 +369,7 @@ k_fin_alpha(const double* partial, int nb, double* scal, int* flags) {
     double alpha;
     const bool bad = step_length(pq, scal[S_RZ], alpha);
     store_step(pq, alpha, bad, scal, flags);
+    if (bad) flags[F_DONE] = 1;
   }
 }
 
@@ -390,9 +391,12 @@ __device__ __forceinline__ void export_wave(const double* scal, int* flags, cons
   }
 }
 
+// (a breakdown of the update before it ends the solve here: F_BREAK is written
+// by no wave of this launch, so all take the same way)
 __global__ void __launch_bounds__(256)
 k_fin_rz(const double* partial, int nb, double* scal, int* flags, HostCopy h) {
-  const bool done = flags[F_DONE] != 0;
+  const bool broken = flags[F_BREAK] != 0, done = broken || flags[F_DONE] != 0;
+  if (broken && threadIdx.x == 0) flags[F_DONE] = 1;
   if (done && !h.seq) return;
   const double rz = done ? 0.0 : fin_sum(partial, nb);
   if (!done && threadIdx.x == 0) {

@@ -43,12 +43,22 @@ def test_shapes_match_oracle(shape):
     assert err <= 1e-6   # both within tol of the limit: ten times the bar of the 1e-11 solves
 
 
-def test_tiled_batch_bit_identical_to_one_at_a_time():
+@pytest.mark.parametrize("shape,counts", [((30, 28, 33), (5, 40, 100, 130)), ((64, 64, 32), (2, 20))],
+                         ids=["8 parts", "16 parts"])
+def test_tiled_batch_bit_identical_to_one_at_a_time(shape, counts):
+    """The workgroups that share a problem depend on the batch (on 256 compute
+    units 8, 4, 2 and 1 of them at the first grid's counts, 16 and 8 at the
+    second's): the bits do not."""
     torch = need_gpu()
     from paper_2502_04217_amd import csipm
-    ws = [_workload((30, 28, 33), s) for s in range(5)]
-    sig, obs = np.stack([w.signal for w in ws]), np.stack([w.observed for w in ws])
-    beta, info = csipm.solve_small_batch(sig, obs, tol=1e-8)
-    for k in (0, 4):
-        b1, i1 = csipm.solve_small_batch(sig[k:k + 1], obs[k:k + 1], tol=1e-8)
-        assert torch.equal(b1[0], beta[k]) and np.array_equal(i1[0], info[k])
+    ws = [_workload(shape, s) for s in range(min(5, max(counts)))]
+    sig, obs = (torch.tensor(np.stack(a), device="cuda") for a in ([w.signal for w in ws], [w.observed for w in ws]))
+    alone = [csipm.solve_small_batch(sig[k:k + 1], obs[k:k + 1], tol=1e-8) for k in range(len(ws))]
+    assert all(i[0, 0] == 0 for _, i in alone)
+    for count in counts:
+        say("small", shape, "count", count)
+        idx = torch.arange(count, device="cuda") % len(ws)
+        beta, info = csipm.solve_small_batch(sig[idx], obs[idx], tol=1e-8)
+        for k in range(count):
+            b1, i1 = alone[k % len(ws)]
+            assert torch.equal(b1[0], beta[k]) and np.array_equal(i1[0], info[k])

@@ -711,9 +711,9 @@ __device__ __forceinline__ void apply(const Ctx& c, Team& team, int mode, double
 // P^{-1} of one 2x2 block (equation "invprecond1", C = I)
 __device__ __forceinline__ void pinv1(double rb, double rz, double s1, double s2, double& zb, double& zz) {
   const double L1 = s1 + s2, L2 = s1 - s2;
-  const double inv = 1.0 / (L1 + 4.0 * s1 * s2);
-  zb = (L1 * rb - L2 * rz) * inv;
-  zz = (-L2 * rb + (1.0 + L1) * rz) * inv;
+  const double D = L1 + 4.0 * s1 * s2;
+  zb = (L1 * rb - L2 * rz) / D;
+  zz = (-L2 * rb + (1.0 + L1) * rz) / D;
 }
 
 // largest a with v + a dv >= 0 over this thread's share (inf if none)

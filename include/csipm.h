@@ -285,7 +285,8 @@ csipm_status csipm_solve_batch(csipm_ctx* const* ctxs, int count, const csipm_op
  * done).  `count` problems of one N1 x N2 x N3 grid, each extent in
  * [1, 64] (any length, odd or even; n = N1*N2*N3), are solved by one kernel,
  * a workgroup (or a team of them, launched cooperatively, for a larger grid in
- * a batch of at most 128) per problem, each to rel_kkt <= opts->tol with the standard
+ * a batch of at most 128; a team that waits 5 s for one of its workgroups gives
+ * up, and one workgroup solves its problem) per problem, each to rel_kkt <= opts->tol with the standard
  * interior-point steps in FP64 and PCG with the paper's preconditioner
  * (section "Primal-dual interior-point method", equations "kkt", "kktmu",
  * "condensedkkt", "invprecond1"; the readings of csipm_solve: starting

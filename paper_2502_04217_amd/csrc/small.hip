@@ -133,11 +133,13 @@ __device__ __forceinline__ void block_reduce(double* v, const int* op, double* r
 
 // ------------------------------------------------------------------ teams --
 // The G workgroups of a problem (one for a resident grid).  All of them take
-// every decision from the same values: a sum is made of kParts parts, part p by
-// workgroup p mod G, combined in order by each, so the bits do not depend on
-// G.  The launch makes sure that all workgroups are resident, and their
-// barrier gives up after kSpinTicks.
-constexpr long long kSpinTicks = 500000000ll;   // 5 s of the 100 MHz clock
+// every decision from the same values: a sum is made of Plan::parts parts,
+// part p by workgroup p mod G, combined in order by each, so the bits do not
+// depend on G.  The launch makes sure that all workgroups are resident together,
+// and a barrier gives up after kTeamWait all the same (work of other streams may
+// hold a compute unit for long): the team then leaves kAbort in its count and
+// ends, and a second launch of one workgroup per problem, which returns at once
+// where the count is clean, solves those problems again.
 constexpr unsigned kAbort = 0x40000000u;
 struct Team {
   int G, rank;
@@ -146,6 +148,7 @@ struct Team {
   double* parts;     // [2][kParts][5] partial sums, used in turn
   int turn;
   int* bad;          // LDS: the barrier gave up
+  long long wait;    // ticks of the 100 MHz clock after which it does
 };
 __device__ __forceinline__ void team_sync(Team& t) {
   // Every wave waits for its own stores before the workgroup's barrier, which
@@ -163,7 +166,7 @@ __device__ __forceinline__ void team_sync(Team& t) {
     unsigned n;
     while ((n = __hip_atomic_load(t.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < t.target) {
       __builtin_amdgcn_s_sleep(1);
-      if (wall_clock64() - t0 > kSpinTicks) {
+      if (wall_clock64() - t0 > t.wait) {
         __hip_atomic_fetch_or(t.count, kAbort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         n = kAbort;
         break;
@@ -723,7 +726,7 @@ __global__ void __launch_bounds__(kMaxThreads)
 k_small_solve(Plan pl, const double* __restrict__ signals, const uint8_t* __restrict__ observed,
               const double* __restrict__ lambdas, double lambda_frac, double* __restrict__ beta_out,
               double* __restrict__ info, char* __restrict__ ws, long long ws_stride, const cx<double>* __restrict__ tw,
-              unsigned* __restrict__ counters, int count, int G, SmallOpts o) {
+              unsigned* __restrict__ counters, int count, int G, SmallOpts o, long long wait, int again) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double red[5 * kMaxWaves];
   __shared__ uint8_t nat[3 * kSmallMaxExtent];
@@ -732,6 +735,7 @@ k_small_solve(Plan pl, const double* __restrict__ signals, const uint8_t* __rest
   // spectrum in that L2)
   const int n = pl.n, prob = G == 1 ? (int)blockIdx.x : (int)blockIdx.x / (8 * G) * 8 + (int)blockIdx.x % 8;
   if (prob >= count) return;
+  if (again && counters[16 * prob] < kAbort) return;   // (solved by its team)
   if (threadIdx.x == 0) bad = 0;
   double* const v = reinterpret_cast<double*>(ws + (long long)prob * ws_stride);
   cx<double>* const twl = reinterpret_cast<cx<double>*>(smem);
@@ -765,7 +769,7 @@ k_small_solve(Plan pl, const double* __restrict__ signals, const uint8_t* __rest
   c.pb_old = c.a(SV_PB2);
   const int parts = pl.parts;
   Team team{G, G == 1 ? 0 : (int)blockIdx.x / 8 % G, 0u, counters + 16 * (G == 1 ? 0 : prob),
-            reinterpret_cast<double*>(c.wg + (pl.resident ? 0 : pl.n1 * pl.n2 * pl.MS)), 0, &bad};
+            reinterpret_cast<double*>(c.wg + (pl.resident ? 0 : pl.n1 * pl.n2 * pl.MS)), 0, &bad, wait};
   // sum (or minimum) over the coordinates, in fixed parts: f(load(i)) with the
   // loads of two coordinates ahead of the first use
   auto over = [&](int op, auto load, auto f) {
@@ -802,10 +806,7 @@ k_small_solve(Plan pl, const double* __restrict__ signals, const uint8_t* __rest
   for (int mode = M_XI;;) {
     double q[5];
     apply(c, team, mode, q);
-    if (bad) {   // (written before a barrier that all have passed)
-      status = -3;
-      break;
-    }
+    if (bad) break;   // (written before a barrier that all have passed)
     if (mode == M_XI) {
       xinf = q[0];
       c.lam = lambdas ? lambdas[prob] : lambda_frac * xinf;
@@ -1069,7 +1070,7 @@ size_t small_problem_bytes(int n1, int n2, int n3) {
 
 hipError_t small_launch(int n1, int n2, int n3, int count, const double* signals, const uint8_t* observed,
                         const double* lambdas, double lambda_frac, double* beta_out, double* info, char* ws,
-                        const cx<double>* tw, unsigned* counters, const SmallOpts& o, hipStream_t s) {
+                        const cx<double>* tw, unsigned* counters, const SmallOpts& o, long long wait, hipStream_t s) {
   if (tiny_grid(n1, n2, n3))
     return tiny_launch(n1, n2, n3, count, signals, observed, lambdas, lambda_frac, beta_out, info, ws, tw, o, s);
   const Plan pl = make_plan(n1, n2, n3);
@@ -1080,7 +1081,7 @@ hipError_t small_launch(int n1, int n2, int n3, int count, const double* signals
     if (e != hipSuccess) return e;
   }
   long long stride = (long long)small_problem_bytes(n1, n2, n3);
-  int G = 1, one = 1;
+  int G = 1, again = 0;
   if (!pl.resident && count <= kSmallTeams) {
     // teams of as many workgroups as are resident together, launched
     // cooperatively (which guarantees it, whatever else the device runs)
@@ -1095,15 +1096,15 @@ hipError_t small_launch(int n1, int n2, int n3, int count, const double* signals
       Plan plan = pl;
       SmallOpts opts = o;
       void* args[] = {&plan, &signals, &observed, &lambdas, &lambda_frac, &beta_out, &info, &ws, &stride, &tw,
-                      &counters, &count, &G, &opts};
+                      &counters, &count, &G, &opts, &wait, &again};
       const hipError_t e = hipLaunchCooperativeKernel((const void*)k_small_solve, dim3((count + 7) / 8 * 8 * G),
                                                       dim3(pl.threads), args, (unsigned)shm, s);
-      if (e == hipSuccess) return e;
-      (void)hipGetLastError();   // (refused: one workgroup per problem)
+      if (e == hipSuccess) again = 1;
+      else (void)hipGetLastError();   // (refused: one workgroup per problem)
     }
   }
   hipLaunchKernelGGL(k_small_solve, dim3(count), dim3(pl.threads), shm, s, pl, signals, observed, lambdas, lambda_frac,
-                     beta_out, info, ws, stride, tw, counters, count, one, o);
+                     beta_out, info, ws, stride, tw, counters, count, 1, o, wait, again);
   return hipGetLastError();
 }
 
@@ -1121,6 +1122,16 @@ extern "C" csipm_status csipm_solve_small_batch(int n1, int n2, int n3, int coun
                                                 double lambda_frac, const csipm_options* opts, double* d_beta_out,
                                                 double* d_info, void* d_workspace, size_t workspace_bytes,
                                                 void* hip_stream) {
+  return csipm_solve_small_batch_wait(n1, n2, n3, count, d_signals, d_observed, d_lambdas, lambda_frac, opts,
+                                      d_beta_out, d_info, d_workspace, workspace_bytes, hip_stream,
+                                      csipm::kTeamWait);
+}
+
+extern "C" csipm_status csipm_solve_small_batch_wait(int n1, int n2, int n3, int count, const double* d_signals,
+                                                     const uint8_t* d_observed, const double* d_lambdas,
+                                                     double lambda_frac, const csipm_options* opts,
+                                                     double* d_beta_out, double* d_info, void* d_workspace,
+                                                     size_t workspace_bytes, void* hip_stream, long long wait) {
   if (count < 1 || !d_signals || !d_observed || !opts || !d_beta_out || !d_info || !d_workspace ||
       (!d_lambdas && !(lambda_frac > 0.0 && std::isfinite(lambda_frac)))) {
     csipm::noctx_set_error("solve_small_batch: bad argument");
@@ -1165,7 +1176,7 @@ extern "C" csipm_status csipm_solve_small_batch(int n1, int n2, int n3, int coun
   if (e == hipSuccess)
     e = csipm::small_launch(n1, n2, n3, count, d_signals, d_observed, d_lambdas, lambda_frac, d_beta_out, d_info,
                             ws + csipm::small_front_bytes(n1, n2, n3), reinterpret_cast<const cx<double>*>(ws),
-                            reinterpret_cast<unsigned*>(ws + ntw * sizeof(cx<double>)), o, s);
+                            reinterpret_cast<unsigned*>(ws + ntw * sizeof(cx<double>)), o, wait, s);
   if (e != hipSuccess) {
     csipm::noctx_set_error(std::string("solve_small_batch: ") + hipGetErrorString(e));
     return CSIPM_EHIP;

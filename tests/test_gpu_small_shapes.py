@@ -62,3 +62,30 @@ def test_tiled_batch_bit_identical_to_one_at_a_time(shape, counts):
         for k in range(count):
             b1, i1 = alone[k % len(ws)]
             assert torch.equal(b1[0], beta[k]) and np.array_equal(i1[0], info[k])
+
+
+def test_team_that_gives_up_is_solved_by_one_workgroup():
+    """With no patience at a team's barrier every team gives up (and its count
+    in the workspace says so); the results are those of patient teams."""
+    torch = need_gpu()
+    import ctypes as C
+    from paper_2502_04217_amd import csipm
+    shape, count = (30, 28, 33), 5
+    ws = [_workload(shape, s) for s in range(count)]
+    sig = torch.tensor(np.stack([w.signal for w in ws]), device="cuda")
+    obs = torch.tensor(np.stack([w.observed for w in ws]).astype(np.uint8), device="cuda")
+    want, winfo = csipm.solve_small_batch(sig, obs, lambda_frac=0.05, tol=1e-8)
+    nb = csipm.small_workspace_bytes(shape, count)
+    buf = torch.empty(nb // 8 + 64, dtype=torch.float64, device="cuda")
+    beta = torch.empty_like(sig)
+    info = torch.empty((count, csipm.SMALL_INFO), dtype=torch.float64, device="cuda")
+    fn = csipm.lib().csipm_solve_small_batch_wait
+    fn.restype, fn.argtypes = C.c_int, csipm.lib().csipm_solve_small_batch.argtypes + [C.c_longlong]
+    off = -buf.data_ptr() % 256
+    st = fn(*shape, count, sig.data_ptr(), obs.data_ptr(), None, 0.05, C.byref(csipm.default_options(tol=1e-8)),
+            beta.data_ptr(), info.data_ptr(), buf.data_ptr() + off, nb, torch.cuda.current_stream().cuda_stream, -1)
+    torch.cuda.synchronize()
+    assert st == 0
+    counts = buf.view(torch.int32)[off // 4 + 4 * sum(shape):][:16 * count:16]
+    assert bool((counts >= 1 << 30).all())
+    assert torch.equal(beta, want) and np.array_equal(info.cpu().numpy(), winfo)

@@ -154,7 +154,7 @@ StridedGeom<T> geom(const Grid& g, int axis) {
 int axis12_tiles(const Grid& g, int axis, int elem_bytes, int dir) {
   const int L = axis == 1 ? g.n1 : g.n2;
   const int batch = axis == 1 ? g.n2 * g.m : g.n1 * g.m;
-  const int tm = g.odd3() && axis == 1 ? any_tm(elem_bytes, L) : pass_tm(elem_bytes, L, axis, dir);
+  const int tm = g.odd3() && axis == 1 ? any_tm(elem_bytes, L, batch) : pass_tm(elem_bytes, L, axis, dir, batch);
   return (batch + tm - 1) / tm;
 }
 

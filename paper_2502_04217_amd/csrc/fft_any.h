@@ -27,9 +27,9 @@
 //
 // These passes are bound by memory and the latency of its pipeline: the
 // transform costs two or three LDS round trips per element (five or six in
-// an axis-3 pass), and a run of TM pencils is one 128-byte line, so that no
-// two workgroups share the lines of an aligned row (xcd_tile: nor two XCDs those
-// of any other).  Against passes that kept
+// an axis-3 pass), and a run of TM pencils is one 128-byte line (less over few
+// pencils, any_few), so that no two workgroups share the lines of an aligned row
+// (xcd_tile: nor two XCDs those of any other).  Against passes that kept
 // the pencil in LDS through Stockham stages of radix 8, 4, 2, 3, 5, 7 (two
 // barriers per stage, 64-byte runs at these lengths), a K-apply takes, in us:
 //   300 x 400 x 400 FP32  1224 -> 705 (2.9 GB: 4.1 TB/s)
@@ -534,6 +534,7 @@ bool launch_axis12_any(int L, dim3 grid, const cx<T>* src, cx<T>* dst, StridedGe
                        int n2, Epi epi, const int* skip, hipStream_t s) {
   AnyPlan plan;
   if (!any_plan(L, (int)sizeof(cx<T>), plan)) return false;
+  any_few(plan, geo.batch, kStridedLowest);
   const int tm = 1 << plan.tmlog;
   const Plane0 pl{n2, AX == 1 && Epi::IO != IO_ODD ? plane0_groups(DIR) : 0};
   const size_t shm = (size_t)(tm + 1) * L * sizeof(cx<T>);   // (the tile and the twiddles)
@@ -571,6 +572,7 @@ bool launch_axis3_odd(int L, int mode, int np, const T* src, T* dst, const uint3
                       T sc_c2r, T sc_dc, T sc_ac, const int* skip, hipStream_t s) {
   AnyPlan plan;
   if (L % 2 == 0 || L < 3 || !any_plan(L, (int)sizeof(cx<T>), plan)) return false;
+  any_few(plan, (np + 1) / 2, 0);
   const int tm = 1 << plan.tmlog;
   const size_t shm = (size_t)L * (tm + 2) * sizeof(cx<T>) + 4 * ((size_t)(2 * tm * L) / 32 + 2);
   const dim3 grid((np + 2 * tm - 1) / (2 * tm)), block(tm * plan.nt);

@@ -32,6 +32,17 @@ bool search(int L, int top, int depth, int* cur, int sum, int* best, int& nbest,
   return ok;
 }
 
+// butterflies of a pencil in the stage of the largest radix
+int butterflies(const AnyPlan& pl) {
+  const int top = *std::max_element(pl.r, pl.r + pl.nst);
+  return (pl.L + top - 1) / top;
+}
+// threads per pencil: as many, within kMaxThreads, in whole waves
+void set_threads(AnyPlan& pl) {
+  const int tm = 1 << pl.tmlog, unit = 64 / tm;
+  pl.nt = std::min((butterflies(pl) + unit - 1) / unit * unit, any::kMaxThreads / tm);
+}
+
 unsigned magic(int d) { return (unsigned)((0x100000000ull + d - 1) / d); }
 
 }  // namespace
@@ -67,20 +78,32 @@ bool any_plan(int L, int w, AnyPlan& pl) {
   pl.hm = L / 2 + 1 > 1 ? magic(L / 2 + 1) : 0u;
   pl.lm = L > 1 ? magic(L) : 0u;
   // pencils per workgroup: a run of one 128-byte line; more (at most 64) while
-  // the pencils are too short for a whole wave.  Threads per pencil: as many
-  // as the stage with the largest radix has butterflies, within kMaxThreads.
-  const int top = *std::max_element(pl.r, pl.r + n);
-  const int least = (L + top - 1) / top;
+  // the pencils are too short for a whole wave.
   pl.tmlog = w == 8 ? 4 : 3;
-  while ((1 << pl.tmlog) * least < 64 && pl.tmlog < 6) ++pl.tmlog;
-  const int tm = 1 << pl.tmlog, unit = 64 / tm;
-  pl.nt = std::min((least + unit - 1) / unit * unit, any::kMaxThreads / tm);
+  while ((1 << pl.tmlog) * butterflies(pl) < 64 && pl.tmlog < 6) ++pl.tmlog;
+  set_threads(pl);
   return true;
 }
 
-int any_tm(int w, int L) {
+// A pass over few long pencils has few workgroups of 16 (FP32) or 8 (FP64), and
+// its time is that of one: narrower ones spread it, though a run of 4 pencils is
+// a part of a line, which such an array's size makes cheap.  Tiles of one line
+// against this, in us, FP32: apply_K at 1000 x 16 x 16 81, 48, at 875 x 16 x 16
+// 68, 42, at 600 x 16 x 16 54, 38; apply_A at 16 x 16 x 875 38.5, 19.4, at
+// 1 x 1024 x 875 50.7, 30.0; apply_At at 1 x 1 x 945 27, 16.  From kFewGroups
+// workgroups on one more compute unit at work is worth less than whole lines.
+void any_few(AnyPlan& pl, long long pencils, int lowest) {
+  const int least = butterflies(pl);
+  while (pl.tmlog > lowest && (pencils + (1 << pl.tmlog) - 1) >> pl.tmlog < kFewGroups && (1 << pl.tmlog) / 2 * least >= 64)
+    --pl.tmlog;
+  set_threads(pl);
+}
+
+int any_tm(int w, int L, int pencils) {
   AnyPlan pl;
-  return any_plan(L, w, pl) ? 1 << pl.tmlog : 1;
+  if (!any_plan(L, w, pl)) return 1;
+  any_few(pl, pencils, kStridedLowest);
+  return 1 << pl.tmlog;
 }
 
 CSIPM_ANY(double)

@@ -1228,8 +1228,12 @@ struct AnyPlan {
 // false when L has a prime factor above 7 or lies outside [1, kAnyMaxLen];
 // w: complex size in bytes
 bool any_plan(int L, int w, AnyPlan& pl);
-// pencils per workgroup at complex size w
-int any_tm(int w, int L);
+// Fewer pencils per workgroup, down to 2^lowest and to one wave's work, while
+// fewer than kFewGroups workgroups would take all of them.
+constexpr int kFewGroups = 128, kStridedLowest = 2;   // (the self-paired rows take four lanes of one workgroup)
+void any_few(AnyPlan& pl, long long pencils, int lowest);
+// pencils per workgroup of a strided pass over so many at complex size w
+int any_tm(int w, int L, int pencils);
 template <typename T, int AX, int DIR, class Epi>
 bool launch_axis12_any(int L, dim3 grid, const cx<T>* src, cx<T>* dst, StridedGeom<T> geo, const cx<T>* tw, int m,
                        int n2, Epi epi, const int* skip, hipStream_t s);
@@ -1243,8 +1247,8 @@ template <typename T>
 bool launch_axis3_odd(int L, int mode, int np, const T* src, T* dst, const uint32_t* maskbits, const cx<T>* tw3,
                       T sc_c2r, T sc_dc, T sc_ac, const int* skip, hipStream_t s);
 // pencils per workgroup of the strided pass that serves length L
-inline int pass_tm(int w, int L, int axis, int dir) {
-  return templated12(L) ? strided_tm(w, L, axis, dir) : any_tm(w, L);
+inline int pass_tm(int w, int L, int axis, int dir, int pencils) {
+  return templated12(L) ? strided_tm(w, L, axis, dir) : any_tm(w, L, pencils);
 }
 
 #define CSIPM_IO(EPI, T, IO) EPI<T, IO>   // (a comma inside a macro argument)

@@ -45,11 +45,15 @@ def plan(L):
     return st if len(st) > 1 else [1] + st
 
 
-def shape(L, st, w):
+def shape(L, st, w, pencils=None, lowest=2):
+    """Pencils per workgroup and threads per pencil; fewer pencils (not below
+    2^lowest) where fewer than 128 workgroups would take them all."""
     least = -(-L // max(st))
     lg = 4 if w == 8 else 3
     while (1 << lg) * least < 64 and lg < 6:
         lg += 1
+    while pencils is not None and lg > lowest and -(-pencils >> lg) < 128 and (1 << lg) // 2 * least >= 64:
+        lg -= 1
     tm = 1 << lg
     unit = 64 // tm
     return tm, min(-(-least // unit) * unit, MAX_THREADS // tm)
@@ -115,6 +119,11 @@ def test_plan_and_transforms(L):
         if L <= 512:
             assert L * (tm + 2) * w + 4 * (2 * tm * L // 32 + 2) <= 163840
         assert tm * max(L, L // 2 + 1) < 65536 or L > 512       # axis-3 run indices
+        for pencils in (1, 7, 60, 127 * tm, 127 * tm + 1, 1000, 10 ** 6):
+            for lowest in (0, 2):   # row pairs, strided passes
+                fm, ft = shape(L, st, w, pencils, lowest)
+                assert (1 << lowest) <= fm <= tm and (fm == tm or -(-pencils // (2 * fm)) < 128)
+                assert fm * ft <= MAX_THREADS and (fm * ft) % 64 == 0 and ft >= min(nt, -(-L // max(st)))
     rng = np.random.default_rng(L)
     x = rng.standard_normal(L) + 1j * rng.standard_normal(L)
     n = np.arange(L)

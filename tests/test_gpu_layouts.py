@@ -2,8 +2,9 @@
 layout, and the row pairs of an odd N3, at the edges of their tiles: every
 operator against the oracle with one extent at a time around the tile widths
 (16 pencils of FP32, 8 of FP64 and their multiples), N3/2 smaller than a
-tile, odd pencil counts (the last row pair has one row), both parities, and
-arrays that start at an odd element (the beta side takes any element
+tile, odd pencil counts (the last row pair has one row), both parities, long
+pencils in numbers that take narrower tiles (down to 4 pencils, and to 1 pair of
+rows), and arrays that start at an odd element (the beta side takes any element
 alignment)."""
 import numpy as np
 import pytest
@@ -16,7 +17,8 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [(4, 3, 6), (5, 7, 4), (8, 1, 32), (16, 2, 32), (6, 6, 14), (9, 16, 30), (18, 5, 10), (64, 3, 16),
           (10, 10, 36), (256, 2, 4), (3, 5, 7), (5, 5, 3), (1, 1, 15), (2, 7, 45), (15, 1, 49), (10, 3, 27),
-          (7, 9, 125), (64, 4, 9), (1, 15, 21)]
+          (7, 9, 125), (64, 4, 9), (1, 15, 21), (3, 1, 945), (1, 1, 945), (9, 27, 315), (1, 63, 75), (980, 3, 6),
+          (600, 16, 16), (2, 735, 10), (75, 2, 60), (315, 5, 15)]
 
 
 def _err(a, b):

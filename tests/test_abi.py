@@ -40,7 +40,7 @@ def test_host_only_calls():
     assert csipm.workspace_bytes((8, 8, 2)) == 0
     assert csipm.workspace_bytes((1, 8, 8)) > 0
     assert csipm.workspace_bytes((15, 21, 8)) > 0
-    assert csipm.workspace_bytes((8, 8, 15)) > 0      # odd N3: the full-spectrum transforms
+    assert csipm.workspace_bytes((8, 8, 15)) > 0      # odd N3: rows two by two
     assert csipm.workspace_bytes((45, 45, 45)) > 0
     assert csipm.workspace_bytes((8, 8, 11)) == 0
     assert csipm.workspace_bytes((80, 100, 120)) > 0

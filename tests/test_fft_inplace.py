@@ -7,7 +7,9 @@ indices stay in the table, and the stages with the kernels' indexing give
 numpy's FFT: decimation in frequency to the slots of block_freq, decimation
 in time from the slots of slot_of, and an axis-3 pass (pairwise packing, the
 last inverse stage, the mask and the first forward stage on the same values,
-pairwise unpacking) numpy's irfft / mask / rfft."""
+pairwise unpacking) numpy's irfft / mask / rfft; so does that of an odd N3,
+which takes the rows two by two, with the mask read from its words, over
+several workgroups and a last row without a partner."""
 import numpy as np
 import pytest
 
@@ -116,9 +118,9 @@ def test_plan_and_transforms(L):
         tm, nt = shape(L, st, w)
         assert tm * nt <= MAX_THREADS and (tm * nt) % 64 == 0 and tm >= 4
         assert (tm + 1) * L * w <= 163840                       # the strided tile and its twiddles
-        if L <= 512:
+        if L <= 512 or L % 2:   # an axis-3 pass (N3 = 2 L, or an odd N3 = L): tile, twiddles and mask words
             assert L * (tm + 2) * w + 4 * (2 * tm * L // 32 + 2) <= 163840
-        assert tm * max(L, L // 2 + 1) < 65536 or L > 512       # axis-3 run indices
+            assert 2 * tm * L < 65536                           # the indices of its runs
         for pencils in (1, 7, 60, 127 * tm, 127 * tm + 1, 1000, 10 ** 6):
             for lowest in (0, 2):   # row pairs, strided passes
                 fm, ft = shape(L, st, w, pencils, lowest)
@@ -186,3 +188,84 @@ def test_axis3_pass(L):
     got = np.empty(L + 1, np.complex128)
     got[0], got[L], got[1:L] = Y[0].real, Y[0].imag, Y[1:] / r2
     assert np.linalg.norm(got - ref) <= 1e-12 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("L", [n for n in LENGTHS if n >= 3 and n % 2])
+def test_odd_axis3_pass(L):
+    """k_axis3_odd: three passes (inverse alone, both with the mask, forward
+    alone) over seven rows in workgroups of two pairs."""
+    st, M, rows, TM = plan(L), (L + 1) // 2, 7, 2
+    rng = np.random.default_rng(L)
+    X = rng.standard_normal((rows, M)) + 1j * rng.standard_normal((rows, M))   # sqrt2 times the half spectra,
+    X[:, 0] = X[:, 0].real                                                     # the real value of e = 0 once
+    mask = rng.random(rows * L) < 0.7
+    words = np.zeros(rows * L // 32 + 1, np.uint32)
+    np.bitwise_or.at(words, np.nonzero(mask)[0] >> 5, np.uint32(1) << (np.nonzero(mask)[0] & 31).astype(np.uint32))
+    real = rng.standard_normal((rows, L))
+    R = st[-1]
+    nbf, q = L // R, np.arange(R)
+    at = np.arange(nbf)[:, None] * R + q[None, :]
+    nat = block_freq(np.arange(nbf), st)[:, None] + nbf * q[None, :]
+    slots = slot_of(np.arange(L), st)
+    r2, rn = np.sqrt(2.0), 1.0 / np.sqrt(L)
+    back = np.full((rows, L), np.nan)
+    full, fwd = (np.full((rows, M), np.nan, np.complex128) for _ in range(2))
+    zero = np.zeros(M, np.complex128)
+    for group in range(-(-rows // (2 * TM))):
+        row0 = 2 * TM * group
+        nrow = min(2 * TM, rows - row0)
+        bit0 = row0 * L
+        nw = ((bit0 + nrow * L - 1) >> 5) - (bit0 >> 5) + 1
+        assert nw <= 2 * TM * L // 32 + 2 and (bit0 >> 5) + nw <= words.size
+        mw = words[bit0 >> 5:(bit0 >> 5) + nw]
+        for p in range(TM):
+            on = [2 * p < nrow, 2 * p + 1 < nrow]
+            x, y = (X[row0 + 2 * p + k] if on[k] else zero for k in (0, 1))
+            for masked in (False, True):
+                a = np.empty(L, np.complex128)
+                a[0] = r2 * x[0].real + 1j * r2 * y[0].real
+                e = np.arange(1, M)
+                a[e] = (x[e].real - y[e].imag) + 1j * (x[e].imag + y[e].real)
+                a[L - e] = (x[e].real + y[e].imag) + 1j * (y[e].real - x[e].imag)
+                for s in range(len(st) - 1):
+                    stage(a, L, st, s, +1, False)
+                v = a[at] @ np.exp(2j * np.pi * np.outer(q, q) / R)
+                if not masked:
+                    a[at] = v
+                    z = a[slots] * (rn / r2)
+                    if on[0]:
+                        back[row0 + 2 * p] = z.real
+                    if on[1]:
+                        back[row0 + 2 * p + 1] = z.imag
+                    continue
+                ba = (bit0 & 31) + 2 * p * L + nat
+                keep = [((mw[(ba + k * L) >> 5] >> ((ba + k * L) & 31).astype(np.uint32)) & 1) if on[k] else 0 for k in (0, 1)]
+                a[at] = (v.real * keep[0] + 1j * v.imag * keep[1]) @ np.exp(-2j * np.pi * np.outer(q, q) / R)
+                for s in range(len(st) - 2, -1, -1):
+                    stage(a, L, st, s, -1, True)
+                unpack(a, L, M, on, row0 + 2 * p, full, rn * rn / r2, rn * rn / 2)
+            a = np.empty(L, np.complex128)
+            a[slots] = (real[row0 + 2 * p] if on[0] else 0.0) + 1j * (real[row0 + 2 * p + 1] if on[1] else 0.0)
+            for s in range(len(st) - 1, -1, -1):
+                stage(a, L, st, s, -1, True)
+            unpack(a, L, M, on, row0 + 2 * p, fwd, rn, rn / r2)
+    half = X / r2
+    half[:, 0] = X[:, 0]
+    sig = np.fft.irfft(half, L, norm="ortho")
+    spec = np.fft.rfft(np.where(mask.reshape(rows, L), sig, 0.0), norm="ortho")
+    spec[:, 1:] *= r2
+    spec2 = np.fft.rfft(real, norm="ortho")
+    spec2[:, 1:] *= r2
+    for got, ref in ((back, sig), (full, spec), (fwd, spec2)):
+        assert np.linalg.norm(got - ref) <= 1e-12 * np.linalg.norm(ref)
+
+
+def unpack(a, L, M, on, row, out, dc, ac):
+    e = np.arange(1, M)
+    y, z = a[e], a[L - e]
+    if on[0]:
+        out[row, 0] = a[0].real * dc
+        out[row, e] = ((y.real + z.real) + 1j * (y.imag - z.imag)) * ac
+    if on[1]:
+        out[row + 1, 0] = a[0].imag * dc
+        out[row + 1, e] = ((y.imag + z.imag) + 1j * (z.real - y.real)) * ac

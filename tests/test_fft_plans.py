@@ -1,9 +1,8 @@
 """The Stockham stage plans of the pencil FFT kernels, restated on the CPU
 (no GPU): for every length the register-resident kernels are instantiated
 at (csrc/fft_kernels.h: Radix<L, E> with the elements per thread of each
-pass) and every length 2^a 3^b 5^c 7^d up to 1024 of the LDS-resident passes
-(csrc/fft_any.hip: the plan computed at launch, TM pencils of NT threads,
-in both precisions' workgroup shapes),
+pass; the other lengths' in-place passes are restated in
+test_fft_inplace.py),
 the stages, run in numpy with the kernels' butterfly indexing, give numpy's
 FFT in both directions; each stage's butterflies are all taken by some
 thread, and its outputs write every element exactly once.  The stage
@@ -55,31 +54,6 @@ def radix_plan(L, E):
     if r > 1:
         st.append(r)
     return st + odd_factors(odd_part(L))
-
-
-def any_plan(L):
-    """The LDS-resident passes' plan: radix 8, then one 4 or 2, then 3, 5, 7."""
-    a, r = 0, L
-    while r % 2 == 0:
-        r //= 2
-        a += 1
-    st = [8] * (a // 3) + ([1 << (a % 3)] if a % 3 else [])
-    for f in (3, 5, 7):
-        while r % f == 0:
-            st.append(f)
-            r //= f
-    return st if r == 1 else None
-
-
-# threads per workgroup of the LDS-resident passes: FP32 512, FP64 256
-ANY_THREADS = {"f32": 512, "f64": 256}
-
-
-def any_tm(threads, L):
-    tm = threads
-    while tm > 1 and tm * L > 4096:
-        tm //= 2
-    return tm
 
 
 def run_stages(x, plan, nthreads, nb_of, direction):
@@ -168,29 +142,6 @@ def test_register_plan(L, E):
     if L == 1:
         return
     check_fft(L, plan, NT, lambda R: -(-(L // R) // NT))
-
-
-SMOOTH = [L for L in range(1, 1025) if any_plan(L) is not None]
-
-
-def test_any_lengths():
-    assert len(SMOOTH) == 143
-    assert all(any_plan(L) is None for L in (11, 13, 22, 1001))
-
-
-@pytest.mark.parametrize("prec", ["f32", "f64"])
-@pytest.mark.parametrize("L", [L for L in SMOOTH if L >= 3])
-def test_any_plan(L, prec):
-    plan = any_plan(L)
-    assert len(plan) <= 12
-    threads = ANY_THREADS[prec]
-    emax = 4096 // threads
-    tm = any_tm(threads, L)
-    nt = threads // tm
-    # the self-paired rows of the axis-1 passes take four lanes of one
-    # workgroup; a thread holds at most emax values (8 in FP32, 16 in FP64)
-    assert tm >= 4 and -(-L // nt) <= emax
-    check_fft(L, plan, nt, lambda R: -(-emax // R))
 
 
 def product_twiddles(w1, r):

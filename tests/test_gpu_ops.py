@@ -23,7 +23,7 @@ MIXED_SHAPES = [(_MIXED[i], _MIXED[(i + 1) % 8], _MIXED[(i + 2) % 8]) for i in r
 LOWDIM_SHAPES = [(1, 64, 64), (1, 1, 256), (2, 96, 40), (1, 560, 12), (64, 1, 32), (2, 2, 8), (1, 1, 4)]
 # odd extents on axes 1 and 2 (no Nyquist index there)
 ODD_SHAPES = [(3, 5, 8), (7, 9, 12), (15, 21, 16), (35, 45, 20), (45, 35, 64), (1, 21, 28), (5, 1, 40), (9, 7, 96)]
-# odd N3 (the full-spectrum transforms), with an even and an odd number of
+# odd N3 (half spectra, the rows two by two), with an even and an odd number of
 # samples (the latter adds a coordinate without data inside the library)
 ODD3_SHAPES = [(8, 8, 15), (15, 21, 35), (45, 45, 45), (3, 5, 7), (1, 1, 9), (1, 16, 21), (12, 20, 5), (2, 4, 3),
                (64, 32, 9)]
@@ -34,15 +34,15 @@ ODD3_SHAPES = [(8, 8, 15), (15, 21, 35), (45, 45, 45), (3, 5, 7), (1, 1, 9), (1,
 # that fills several workgroups of each pass at L = 256
 BENCH_SHAPES = [(256, 16, 8), (16, 256, 8), (8, 8, 256), (512, 4, 8), (4, 512, 8), (4, 4, 512), (256, 64, 16),
                 (16, 32, 256)]
-# extents 2^a 3^b 5^c 7^d without instantiated kernels (the passes with the
-# pencils in LDS and a radix plan computed at launch): each radix on every
+# extents 2^a 3^b 5^c 7^d without instantiated kernels (the in-place passes
+# with a radix plan computed at launch): each radix on every
 # axis, odd and even, the axis-3 half lengths 9, 5, 7, 60, 25 and 500, the
-# longest pencils (1000 = 2^3 5^3, four per workgroup) on each axis, odd N3
-# of such lengths (the full-spectrum transforms at 63 and 875), and 2D grids
+# longest pencils (1000 = 2^3 5^3, down to four per workgroup) on each axis, odd N3
+# of such lengths (63 and 875), and 2D grids
 ANY_SHAPES = [(6, 10, 18), (18, 14, 10), (10, 6, 14), (80, 100, 120), (25, 27, 50), (1000, 6, 4), (6, 1000, 4),
               (4, 6, 1000), (49, 63, 8), (14, 10, 63), (6, 4, 875), (1, 50, 42), (160, 1, 6)]
 # 16 shapes drawn (numpy default_rng(20261203)) from the 7-smooth extents 3-64 on every axis: register-
-# and LDS-resident lengths mixed within one grid, odd N3 (the full-spectrum transforms) and even N3
+# resident and in-place lengths mixed within one grid, odd N3 and even N3
 # with odd half lengths
 RANDOM_SHAPES = [(64, 50, 48), (32, 35, 9), (24, 18, 12), (28, 35, 4), (9, 3, 20), (60, 42, 27), (24, 36, 64),
                  (27, 21, 14), (48, 21, 20), (12, 30, 45), (60, 25, 5), (4, 27, 36), (27, 5, 12), (60, 27, 4),

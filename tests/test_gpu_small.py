@@ -1,4 +1,4 @@
-"""csipm_solve_small_batch (one kernel, one workgroup per problem) against
+"""csipm_solve_small_batch (a workgroup or a team per problem) against
 the oracle's interior-point solve, against the library's csipm_solve, and
 batched against one problem at a time (bit for bit)."""
 import numpy as np
@@ -27,9 +27,9 @@ def _batch(ws, lams=None, **kw):
 def test_small_batch_matches_oracle(shape):
     """Each problem of a batch reaches the oracle's LASSO solution (both
     stopped at rel_kkt 1e-11) with the oracle's interior-point iteration
-    count up to one.  The shapes cover the register pencils (2 to 32), the
-    direct DFTs of other lengths (with their scratch buffer), spectra in
-    LDS (up to 128 KB) and in the workspace (32^3, 24 x 40 x 12)."""
+    count up to one.  The shapes cover the whole spectrum with direct DFTs (1 x 16 x 24,
+    8 x 6 x 5), half spectra in the LDS of one workgroup (up to 16 x 16 x 32)
+    and in the workspace, solved by a team (32^3, 24 x 40 x 12)."""
     if shape == (16, 16, 16):
         ws = [wl.grid16(s) for s in (1, 2, 3)]
     else:

@@ -122,7 +122,7 @@ def test_mixed_grid_parity(shape, half, period, dropout, precision):
     """Grids with odd factors 3, 5 and 7 (odd-radix FFT stages on every
     axis), a 2D grid (1 x 64 x 96), a 1D one (1 x 1 x 512), grids with odd
     extents on axes 1 and 2 (15 x 21 x 32, 45 x 35 x 8) and with an odd N3
-    (the full-spectrum transforms: 8 x 16 x 45; 15 x 21 x 35 and 45^3, whose
+    (rows two by two: 8 x 16 x 45; 15 x 21 x 35 and 45^3, whose
     odd sample counts add a coordinate without data inside the library),
     and grids of extents without instantiated kernels (18 x 20 x 30,
     50 x 36 x 42, 27 x 21 x 14, and 14 x 10 x 63 and 12 x 30 x 45 with an odd

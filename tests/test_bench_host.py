@@ -54,3 +54,12 @@ def test_working_launch_threshold():
     assert bench.working_min_us((256, 256, 256)) == pytest.approx(0.8 * 2 * 256 ** 3 * 4 / 8e12 * 1e6)
     assert 13.0 < bench.working_min_us((256, 256, 256)) < 14.0
     assert bench.working_min_us((64, 64, 64)) == 8.0
+
+
+def test_profile_summary_names_kernels_without_namespaces():
+    from paper_2502_04217_amd.rocprof_summary import short
+    assert short("void csipm::fftk::any::k_axis12_any<float, 1, -1, csipm::fftk::EpiK<float> >(csipm::cx<float> const*)") \
+        == "k_axis12_any<float, 1, -1, EpiK<float> >"
+    assert short("void csipm::fftk::cube::k_cube<double, csipm::fftk::EpiIn<double, 1>, csipm::fftk::cube::Real>(int)") \
+        == "k_cube<double, EpiIn<double, 1>, Real>"
+    assert short("csipm::(anonymous namespace)::k_fin_rz(double const*)") == "k_fin_rz"

@@ -89,3 +89,33 @@ def test_team_that_gives_up_is_solved_by_one_workgroup():
     counts = buf.view(torch.int32)[off // 4 + 4 * sum(shape):][:16 * count:16]
     assert bool((counts >= 1 << 30).all())
     assert torch.equal(beta, want) and np.array_equal(info.cpu().numpy(), winfo)
+
+
+def test_batches_of_several_threads_and_streams():
+    """Cooperative launches queued by two threads on streams of their own give
+    the bits of a call alone."""
+    torch = need_gpu()
+    import threading
+    from paper_2502_04217_amd import csipm
+    data = []
+    for shape, count in (((30, 28, 33), 16), ((32, 32, 32), 24)):
+        ws = [_workload(shape, s) for s in range(4)]
+        idx = torch.arange(count, device="cuda") % 4
+        sig, obs = (torch.tensor(np.stack(a), device="cuda")[idx] for a in ([w.signal for w in ws], [w.observed for w in ws]))
+        data.append((sig, obs, csipm.solve_small_batch(sig, obs, tol=1e-8)[0]))
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for r in range(4):
+                sig, obs, want = data[(k + r) % 2]
+                if not torch.equal(csipm.solve_small_batch(sig, obs, tol=1e-8)[0], want):
+                    wrong.append((k, r))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong

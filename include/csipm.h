@@ -365,6 +365,9 @@ csipm_status csipm_set_pc_params(csipm_ctx* ctx, const float* d_params, int n_pa
 
 /* Network kernels (stateless; queued on hip_stream; no allocation):
  *   forward  : c[i] = softplus(MLP(feat[i][0..3])) + 1e-6, i < n_rec
+ *              (the W2 product from three bf16 places of each factor, 24
+ *              bits: a W2 weight beyond 1.17e38, an infinity too, acts as
+ *              1.17e38, here and in csipm_solve's correction)
  *   backward : grad += d/dparams sum_i dc[i] c[i]
  *   loss_grad: loss_out[0] = sum_i w_i (L1_i^2 + L2_i^2)(u_i - c_i p_i)^2 /
  *              (L1_i + S12_i)^2 (the i-th block of P^{-1}(K - P_c)p squared,

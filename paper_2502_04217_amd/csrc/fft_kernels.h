@@ -564,13 +564,22 @@ struct StridedGeom {
 // tiles and had 32 of 64 KB), large ones by loads in flight, which many small
 // workgroups on a compute unit keep up across each other's barriers.  The
 // forward pass of axis 1 also streams the vectors of its epilogue and takes
-// rows of 256 bytes.  apply_K in microseconds, tiles of 64 to 128 KB with 16
-// elements per thread in most passes against these, FP64 / FP32:
-//   64^3 33.6, 26.6 / 24.5, 21.5;  128^3 72, 47.6 / 68.4, 45.7;
-//   192^3 189, 113 / 177, 91.6;    256^3 382, 196 / 371, 181;
-//   384^3 1409, 739 / 1402, 707;   512^3 FP32 1664 / 1654;
-//   512 x 512 x 384 FP64 2490 / 2515, within what its runs differ by (80).
-// Rows of 256 bytes on the inverse pass of axis 1 take 3 % longer at 256^3
+// rows of 256 bytes.  The rule is made for complex rows, those of the internal
+// layout; an axis-1 pass on the external one reads each row as two runs of half
+// the bytes.  Microseconds, tiles of 64 to 128 KB with 16 elements per thread in
+// most passes -> these: a K-apply in the internal layout (replayed from a graph),
+// and apply_K, which works on the external one:
+//                    K-apply FP64   FP32          apply_K FP64   FP32
+//   32^3             27.0 -> 20.5   22.6 -> 18.9   32 -> 24       28 -> 23
+//   64^3             33.7 -> 24.4   26.7 -> 21.5   38 -> 29       31 -> 26
+//   128^3            72 -> 68       47 -> 45       79 -> 75       51 -> 49
+//   192^3            190 -> 177     113 -> 91      202 -> 190     122 -> 102
+//   256^3            382 -> 371     195 -> 186     441 -> 458     228 -> 218
+//   384^3            1410 -> 1414   742 -> 716     1541 -> 1545   820 -> 798
+//   512 x 512 x 384  2509 -> 2540   1291 -> 1279   2753 -> 2915   1618 -> 1643
+//   512^3            3300 -> 3377   1666 -> 1668   3648 -> 3804   2173 -> 2167
+// (the axis-1 passes of the largest FP64 grids, 332 -> 343 us for the inverse one
+// at 512 x 512 x 384, were better off with 64 KB).  Rows of 256 bytes on the inverse pass of axis 1 take 3 % longer at 256^3
 // and 384^3 in FP32, on axis 2 50 % longer at 384^3; rows of 128 bytes on the
 // forward pass 4 % longer at 256^3 in FP32.  Pencils with odd factors take
 // mixed_e elements per thread, powers of two 8; of the FP32 pencils of 1024,

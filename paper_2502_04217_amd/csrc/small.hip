@@ -26,12 +26,16 @@
 // What bounds it: for a resident grid the chain of stages (12 at 16^3, a
 // barrier each, 2-3 thousand cycles) and the passes over the vectors at the 28
 // bytes per cycle that one compute unit reaches; for a team that rate times its
-// workgroups, and its four barriers per Krylov step (6.8 us each).  Against
-// complex transforms of the whole spectrum, a pencil per thread in registers
-// (2 to 32 points) or direct DFTs in the workspace, one workgroup per problem,
-// a batch takes, in ms: 64 of 16^3 2.6 -> 2.0; 32 of 48 x 40 x 36 397 -> 8.8;
-// 64 of 32^3 29.6 -> 8.7; 16 of 64^3 2810 -> 16; 50 of 24^3 38 -> 4.8.
-// Sixteen waves of 128 registers instead of eight of 232 spill and lose a
+// workgroups, and its four barriers per Krylov step (7 us each with 32 teams on
+// the chip, 1.5 us for one alone).  Against complex transforms of the whole
+// spectrum, a pencil per thread in registers (2 to 32 points) or direct DFTs in
+// the workspace, one workgroup per problem, a batch takes, in ms: 64 of 16^3
+// 2.6 -> 2.0; 32 of 48 x 40 x 36 397 -> 8.8; 64 of 32^3 29.6 -> 8.7; 16 of 64^3
+// 2810 -> 16; 50 of 24^3 38 -> 4.8.  For the larger of these grids
+// csipm_solve_batch was the better route before: on 8 host threads it took 35 ms
+// for 32 problems of 48 x 40 x 36 that take 9.6 here, 57 for 64 of 32^3 (10.3),
+// 28 for 16 of 64^3 (20.5).
+// Sixteen waves of 128 registers instead of eight of 170 spill and lose a
 // quarter.  A problem's result does not depend on the others in the batch: a
 // batch of one gives the same bits.
 #include "small.h"
@@ -179,9 +183,9 @@ __device__ __forceinline__ void team_sync(Team& t) {
 }
 
 // ----------------------------------------------------------------- stages --
-// Calls f(std::integral_constant<int, R>) for the runtime radix r <= 8 (an
-// FP64 radix-10 butterfly does not fit the 128 registers of a workgroup of
-// 1024 threads beside the solver's state).
+// Calls f(std::integral_constant<int, R>) for the runtime radix r <= 8 (with 9
+// and 10 as well every batch takes longer: 64 of 16^3 1.88 -> 1.94 ms, 32 of
+// 48 x 40 x 36 9.65 -> 9.75, 64 of 32^3 10.3 -> 10.45).
 constexpr int kMaxRadix = 8;
 template <class F>
 __device__ __forceinline__ void with_radix(int r, F f) {
